@@ -49,7 +49,9 @@ typedef int32_t gtod_status;
 typedef struct gtod_ctx gtod_ctx;
 
 /* contraction precision */
-#define GTOD_PREC_FP32 0        /* FP32 MFMA, FP32 accumulation          */
+#define GTOD_PREC_FP32 0        /* FP32 operands as two FP16 halves (22
+                                   bits; FP32 MFMA for rows beyond their
+                                   range), FP32 accumulation             */
 #define GTOD_PREC_SPLIT_BF16 1  /* hi+lo BF16 MFMA, FP32 accumulation    */
 
 /* init flags */

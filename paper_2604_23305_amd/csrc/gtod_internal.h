@@ -67,18 +67,21 @@ constexpr int kPanelMaxBuckets = 1 << 16;
 struct GemmArgs {
   const float* panel;    // [rows][Fp] deviations dP
   const float* B;        // [3][Kp][Fp] B0, B1', B2 (fp32)
-  const uint16_t* Bh;    // [3][Kp][Fp] bf16 hi
-  const uint16_t* Bl;    // [3][Kp][Fp] bf16 lo
-  const uint16_t* Bt;    // split responses tiled for the BF16 kernel
+  const uint16_t* Tb;    // BF16 halves of the responses, tiled
+  const uint16_t* Th;    // FP16 halves, tiled, each channel scaled
+  const double* unit0;   // [Kp] worth of an FP16-path C0 unit (W)
+  const double* unit1;   // [Kp] worth of an FP16-path C1 unit (W^2/Hz)
   const double* c0;      // [Kp] reference P_KID
   const double* c1;      // [Kp] reference NEP^2
   int Fp, K, Kp;
   int p0, n_pix, Tc, Tpad;
   int64_t t0, out_t0, out_ld;
   float fs_half;
-  // The panel carries spectral powers times 2^pexp (power-of-two scale,
-  // exact) so that dP and dP^2 stay in the normal FP32 range; the
-  // epilogue multiplies by pinv = 2^-pexp.
+  // The panel carries bin j's spectral power times 2^(pexp + d_j) and the
+  // responses 2^-d_j (2^-2 d_j for B2), powers of two chosen so that every
+  // bin's reference power lies in [2, 4): the products carry 2^pexp, which
+  // keeps them in the normal FP32 range, and the epilogue multiplies by
+  // pinv = 2^-pexp.
   double pinv;
   float pinv_f;
   uint32_t key0, key1;
@@ -91,7 +94,6 @@ struct GemmArgs {
   float* tod;
   float* p_kid;
   float* sigma;
-  int n_tt;              // 128-row time tiles of the chunk
   int n_cg;              // channel groups (set by each contraction launcher)
 };
 
@@ -139,7 +141,6 @@ struct SpecSetupArgs {
   double* B0_64;            // [F][K] B0 = w eta, FP64
   double* B64;              // [2][F][K] scratch (B1, B2)
   float* B;                 // [3][Kp][Fp]
-  uint16_t* Bh; uint16_t* Bl;
   double* c0; double* c1;   // [Kp]
 };
 
@@ -267,16 +268,19 @@ int launch_reduce_grid(const ReduceArgs& a, hipStream_t s);  // 0 ok
 void launch_reduce_combine(const ReduceArgs& a, hipStream_t s);
 void launch_spec_setup(const SpecSetupArgs& a, const PassTable& pt,
                        hipStream_t s);
-void launch_scale_spectra(float* E, float* D, float* W, float* Pref, int Fp,
-                          float scale, hipStream_t s);
+// E, D, W, Pref times sx[j] and the responses times sb[j] (B2: twice).
+void launch_scale_bins(float* E, float* D, float* W, float* Pref, float* B, int Kp, int Fp,
+                       const float* sx, const float* sb, hipStream_t s);
 void launch_panel(const PanelArgs& a, hipStream_t s);
 void launch_gemm_f32(const GemmArgs& a, hipStream_t s);
 void launch_gemm_bf16(const GemmArgs& a, hipStream_t s);
-// Bytes of the tiled split responses of a Kp x Fp setup, and the kernel
-// that builds them from the hi / lo planes.
-size_t split_tiled_bytes(int Kp, int Fp);
-void launch_tile_split_responses(const uint16_t* Bh, const uint16_t* Bl, uint16_t* Bt,
-                                 int Kp, int Fp, float b2_scale, hipStream_t s);
+// Bytes of the tiled halves of a Kp x Fp setup's responses, and the kernels
+// that build them (with the FP16 halves' channel scales e0, e1, unit0,
+// unit1) from the FP32 responses.
+size_t tiled_response_bytes(int Kp, int Fp, bool f16);
+void launch_tile_responses(const float* B, int* e0, int* e1, double* unit0, double* unit1,
+                           uint16_t* Tb, uint16_t* Th, int Kp, int Fp, int pexp,
+                           hipStream_t s);
 void launch_pink_tables(const PinkArgs& a, hipStream_t s);
 void launch_pink_pass1(const PinkArgs& a, hipStream_t s);
 void launch_pink_pass2(const PinkArgs& a, hipStream_t s);

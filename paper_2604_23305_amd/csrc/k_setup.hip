@@ -40,16 +40,6 @@ __device__ double jn_power(double nu, double T) {
   return kH * nu / expm1(kH * nu / (kKB * T));
 }
 
-__device__ uint16_t bf16_rne(float x) {
-  uint32_t b = __float_as_uint(x);
-  b += 0x7FFFu + ((b >> 16) & 1u);
-  return (uint16_t)(b >> 16);
-}
-
-__device__ float bf16_to_f(uint16_t h) {
-  return __uint_as_float(((uint32_t)h) << 16);
-}
-
 // Pass efficiency types, see gtod_runtime: 0 array, 1 constant, 2 Ohmic,
 // 3 dielectric absorption, 4 dielectric surface.
 __device__ double pass_eta(int type, const double* pool, int off, double p0,
@@ -161,9 +151,6 @@ __global__ void k_filters(SpecSetupArgs a) {
     for (int m = 0; m < 3; ++m) {
       const int64_t o = m * KF + (int64_t)k * a.Fp + j;
       a.B[o] = v[m];
-      const uint16_t hi = bf16_rne(v[m]);
-      a.Bh[o] = hi;
-      a.Bl[o] = bf16_rne(v[m] - bf16_to_f(hi));
     }
   }
 }
@@ -199,20 +186,32 @@ __global__ __launch_bounds__(256) void k_reference(SpecSetupArgs a) {
   }
 }
 
-__global__ void k_scale_spectra(float* E, float* D, float* W, float* Pref,
-                                int Fp, float scale) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= Fp) return;
-  E[j] *= scale;
-  D[j] *= scale;
-  W[j] *= scale;
-  Pref[j] *= scale;
+// One block per padded channel for its responses, the last one for the
+// spectra.
+__global__ __launch_bounds__(256) void k_scale_bins(float* E, float* D, float* W, float* Pref,
+                                                    float* B, int Kp, int Fp,
+                                                    const float* sx, const float* sb) {
+  const int k = blockIdx.x;
+  const int64_t KF = (int64_t)Kp * Fp;
+  for (int j = threadIdx.x; j < Fp; j += 256) {
+    if (k == Kp) {
+      E[j] *= sx[j];
+      D[j] *= sx[j];
+      W[j] *= sx[j];
+      Pref[j] *= sx[j];
+    } else {
+      float* b = B + (int64_t)k * Fp + j;
+      b[0] *= sb[j];
+      b[KF] *= sb[j];
+      b[2 * KF] *= sb[j] * sb[j];
+    }
+  }
 }
 
-void launch_scale_spectra(float* E, float* D, float* W, float* Pref, int Fp,
-                          float scale, hipStream_t s) {
-  hipLaunchKernelGGL(k_scale_spectra, dim3((Fp + 127) / 128), dim3(128), 0, s,
-                     E, D, W, Pref, Fp, scale);
+void launch_scale_bins(float* E, float* D, float* W, float* Pref, float* B, int Kp, int Fp,
+                       const float* sx, const float* sb, hipStream_t s) {
+  hipLaunchKernelGGL(k_scale_bins, dim3(Kp + 1), dim3(256), 0, s, E, D, W, Pref, B, Kp, Fp,
+                     sx, sb);
 }
 
 void launch_spec_setup(const SpecSetupArgs& a, const PassTable& pt,

@@ -37,12 +37,13 @@ struct SpecObj {
   float* W = nullptr;
   float* Pref = nullptr;
   float* B = nullptr;
-  uint16_t* Bh = nullptr;
-  uint16_t* Bl = nullptr;
-  uint16_t* Bt = nullptr;   // Bh / Bl tiled for the split contraction
+  uint16_t* Tb = nullptr;   // BF16 halves of the responses, tiled
+  uint16_t* Th = nullptr;   // FP16 halves, tiled, each channel scaled
+  double* unit0 = nullptr;  // worth of the scaled channels' sums
+  double* unit1 = nullptr;
   double* c0 = nullptr;
   double* c1 = nullptr;
-  int pexp = 0;   // the panel carries spectral powers times 2^pexp
+  int pexp = 0;   // the contraction's products carry 2^pexp
   std::vector<double> nep2ref;
   // FP64 tables kept for the skydip, and its brightness-temperature scale
   double t_atm = 0;
@@ -721,9 +722,10 @@ gtod_status gtod_load_filters(gtod_ctx* c, const gtod_spectral_desc* d, int32_t*
   res((void**)&so.W, Fp * 4);
   res((void**)&so.Pref, Fp * 4);
   res((void**)&so.B, 3 * Kp * Fp * 4);
-  res((void**)&so.Bh, 3 * Kp * Fp * 2);
-  res((void**)&so.Bl, 3 * Kp * Fp * 2);
-  res((void**)&so.Bt, split_tiled_bytes((int)Kp, (int)Fp));
+  res((void**)&so.Tb, tiled_response_bytes((int)Kp, (int)Fp, false));
+  res((void**)&so.Th, tiled_response_bytes((int)Kp, (int)Fp, true));
+  res((void**)&so.unit0, Kp * 8);
+  res((void**)&so.unit1, Kp * 8);
   res((void**)&so.c0, Kp * 8);
   res((void**)&so.c1, Kp * 8);
   res((void**)&so.tau64, (size_t)d->n_pwv * F * 8);
@@ -739,7 +741,8 @@ gtod_status gtod_load_filters(gtod_ctx* c, const gtod_spectral_desc* d, int32_t*
   };
   double *d_nu, *d_w, *d_eta, *d_pool, *d_prm, *d_T, *d_f = nullptr, *d_R = nullptr,
          *d_pk = nullptr, *d_mat = nullptr, *d_pref64, *d_B64;
-  int *d_type, *d_coup, *d_off, *d_order;
+  int *d_type, *d_coup, *d_off, *d_order, *d_e;
+  float* d_scale;
   tmpa((void**)&d_nu, F * 8);
   tmpa((void**)&d_w, F * 8);
   tmpa((void**)&d_eta, (size_t)d->n_pwv * F * 8);
@@ -750,6 +753,8 @@ gtod_status gtod_load_filters(gtod_ctx* c, const gtod_spectral_desc* d, int32_t*
   tmpa((void**)&d_coup, std::max<size_t>(pcoup.size(), 1) * 4);
   tmpa((void**)&d_off, std::max<size_t>(poff.size(), 1) * 4);
   tmpa((void**)&d_order, K * 4);
+  tmpa((void**)&d_e, 2 * Kp * 4);
+  tmpa((void**)&d_scale, 2 * Fp * 4);
   tmpa((void**)&d_pref64, Fp * 8);
   tmpa((void**)&d_B64, (size_t)2 * F * K * 8);
   if (d->filter_mode == GTOD_FILT_MATRIX) {
@@ -789,8 +794,6 @@ gtod_status gtod_load_filters(gtod_ctx* c, const gtod_spectral_desc* d, int32_t*
     cp(d_pk, d->eta_peak, K * 8);
   }
   if (e == hipSuccess) e = hipMemset(so.B, 0, 3 * Kp * Fp * 4);
-  if (e == hipSuccess) e = hipMemset(so.Bh, 0, 3 * Kp * Fp * 2);
-  if (e == hipSuccess) e = hipMemset(so.Bl, 0, 3 * Kp * Fp * 2);
   if (e == hipSuccess) {
     SpecSetupArgs a{};
     a.F = F;
@@ -830,8 +833,6 @@ gtod_status gtod_load_filters(gtod_ctx* c, const gtod_spectral_desc* d, int32_t*
     a.B0_64 = so.B0_64;
     a.B64 = d_B64;
     a.B = so.B;
-    a.Bh = so.Bh;
-    a.Bl = so.Bl;
     a.c0 = so.c0;
     a.c1 = so.c1;
     PassTable pt{n_pass, d_type, d_coup, d_off, d_prm, d_T, d_pool};
@@ -844,18 +845,28 @@ gtod_status gtod_load_filters(gtod_ctx* c, const gtod_spectral_desc* d, int32_t*
     e = hipMemcpy(so.nep2ref.data(), so.c1, K * 8, hipMemcpyDeviceToHost);
   }
   if (e == hipSuccess) {
-    // power-of-two scale bringing the largest reference power to [1, 2)
+    // power-of-two scales bringing every bin's reference power to [2, 4)
+    // (a bin below 2^-20 of the largest is scaled as one at 2^-20)
     std::vector<double> pref(Fp);
     e = hipMemcpy(pref.data(), d_pref64, Fp * 8, hipMemcpyDeviceToHost);
     double mx = 0.0;
     for (double v : pref) mx = std::max(mx, std::fabs(v));
-    so.pexp = (mx > 0.0 && std::isfinite(mx)) ? -std::ilogb(mx) : 0;
+    so.pexp = (mx > 0.0 && std::isfinite(mx)) ? 1 - std::ilogb(mx) : 0;
     so.pexp = std::max(-60, std::min(so.pexp, 100));
+    std::vector<float> sc(2 * Fp);
+    for (int64_t j = 0; j < Fp; ++j) {
+      const double v = std::fabs(pref[j]);
+      const int d = (v > 0.0 && std::isfinite(v))
+          ? std::max(0, std::min(1 - std::ilogb(v) - so.pexp, 20)) : 0;
+      sc[j] = std::ldexp(1.0f, so.pexp + d);
+      sc[Fp + j] = std::ldexp(1.0f, -d);
+    }
+    cp(d_scale, sc.data(), 2 * Fp * 4);
     if (e == hipSuccess) {
-      launch_scale_spectra(so.E, so.D, so.W, so.Pref, so.Fp,
-                           std::ldexp(1.0f, so.pexp), nullptr);
-      launch_tile_split_responses(so.Bh, so.Bl, so.Bt, so.Kp, so.Fp,
-                                  std::ldexp(1.0f, -so.pexp), nullptr);
+      launch_scale_bins(so.E, so.D, so.W, so.Pref, so.B, so.Kp, so.Fp, d_scale, d_scale + Fp,
+                        nullptr);
+      launch_tile_responses(so.B, d_e, d_e + Kp, so.unit0, so.unit1, so.Tb, so.Th, so.Kp,
+                            so.Fp, so.pexp, nullptr);
       e = hipGetLastError();
       if (e == hipSuccess) e = hipDeviceSynchronize();
     }
@@ -1055,9 +1066,10 @@ static gtod_status simulate(gtod_ctx* c, const gtod_job* jobs, int32_t n_jobs,
     GemmArgs ga{};
     ga.panel = w->panel;
     ga.B = f.B;
-    ga.Bh = f.Bh;
-    ga.Bl = f.Bl;
-    ga.Bt = f.Bt;
+    ga.Tb = f.Tb;
+    ga.Th = f.Th;
+    ga.unit0 = f.unit0;
+    ga.unit1 = f.unit1;
     ga.c0 = f.c0;
     ga.c1 = f.c1;
     ga.Fp = f.Fp;
@@ -1098,7 +1110,6 @@ static gtod_status simulate(gtod_ctx* c, const gtod_job* jobs, int32_t n_jobs,
         ga.t0 = tb;
         ga.Tc = Tc;
         ga.Tpad = Tpad;
-        ga.n_tt = (int)((int64_t)np * Tpad / kRowPad);
         if (plan[i].precision == GTOD_PREC_SPLIT_BF16)
           timed(c, GTOD_KERNEL_GEMM_BF16, flop, s, [&] { launch_gemm_bf16(ga, s); });
         else

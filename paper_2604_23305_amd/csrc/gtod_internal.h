@@ -60,9 +60,17 @@ struct PanelArgs {
   int n_buckets;         // coarse cells + 1; 1 = no sort
   int cell_shift;        // coarse cell = (el cell >> s, az cell >> s)
   int n_az_coarse;
+  int rows_wg;           // rows per workgroup (set by the launcher)
 };
 constexpr int kPanelRowInfoBytes = 48;   // sizeof(RowInfo) rounded up
 constexpr int kPanelMaxBuckets = 1 << 16;
+// Jobs with a source and at least this many rows sort them by source cell;
+// a stare's rows share their cells as they come.  The four kernels of the
+// sort take 13 to 15 us (55 x 55 grid) up to 28 us (121 x 121) at any small
+// size; what they save grows with the rows: 1000 rows of 3000 bins take 23
+// us in their own order and 38 sorted, 8000 rows 59 and 57, 14700 rows over
+// the larger grid 107 and 109, 32000 rows 184 and 127.
+constexpr int64_t kPanelSortRows = 12288;
 
 struct GemmArgs {
   const float* panel;    // [rows][Fp] deviations dP

@@ -11,16 +11,27 @@
 //   xi    = -expm1(-csc tau_z)                     1 - eta_z^csc
 //   P     = E + xi D + (1 - xi) W P_src            collapsed cascade
 //   dP    = P - Pref
-// A workgroup handles kPanelRows rows; threads stride over nu so that every
-// table, cube and panel access is a contiguous run along nu.
+// A workgroup handles up to kPanelRows rows; a lane takes four bins at a
+// time, so that every table, cube and panel access is a contiguous run along
+// nu, and all rows of a pass of 1024 bins before the next pass.
 //
 // With a source cube, a scan that moves a cell or more per sample makes
 // consecutive samples read different cube corners (four spectra of F
 // floats each), which then come from beyond the L2 for almost every row.
-// The rows of a chunk are therefore first bucketed by the (coarse) cube
-// cell they read, with a counting sort, and the workgroups take them in
-// bucket order: rows that share corners run together.  Each row's result
-// does not depend on the order, only the cache traffic does.
+// The rows of a large chunk are therefore first bucketed by the (coarse)
+// cube cell they read, with a counting sort, and the workgroups take them in
+// bucket order: rows that share corners run together, and a workgroup keeps
+// the corners of its current cell in registers.  Each row's result does not
+// depend on the order, only the cache traffic does.
+//
+// What bounds it: HBM.  A launch of 527k IFU rows writes 6.3 GB of panel and
+// fetches 1.35 GB (5.4 GB when a workgroup took 4 rows over all bins at a
+// time and read their corners again for the next 4) in 1.37 ms, 5.6 TB/s;
+// the five kernels together take 1.49 ms, against 2.43 ms before.  On the
+// way there it was bound by its instructions (41 per element with vector
+// records and the library's expm1f, 32 now) and by the panel's stores
+// displacing the tables from the L2: stored past the caches the sorted
+// kernel went from 1.70 to 1.37 ms.
 #include <hip/hip_runtime.h>
 
 #include "gtod_internal.h"
@@ -36,7 +47,7 @@ struct RowInfo {
   float lw;        // weight of the row above
   float csc;
   int src;         // pointing inside the source grid
-  float wa, we;    // source weights along az / el
+  float w[4];      // weights of corners (el, az), (el, az + 1), (el + 1, az), ...
   int64_t sbase;   // offset of corner (el, az) in the cube
 };
 static_assert(sizeof(RowInfo) <= kPanelRowInfoBytes, "row record");
@@ -51,9 +62,9 @@ __device__ inline void clamp_cell(double g, int64_t n, int64_t* cell,
   *w = gc - (double)c;
 }
 
-// Row quantities of row r (FP64 geometry), the PWV output and the range
-// counters; *bucket gets the row's sort bucket.
-__device__ RowInfo row_info(const PanelArgs& a, int64_t r, uint32_t* bucket) {
+// Row quantities of row r (FP64 geometry); *bucket gets the row's sort
+// bucket.  first: also write the PWV output and count the range events.
+__device__ RowInfo row_info(const PanelArgs& a, int64_t r, uint32_t* bucket, bool first) {
   RowInfo q{};
   *bucket = (uint32_t)(a.n_buckets - 1);
   const int pl = (int)(r / a.Tpad);
@@ -76,20 +87,20 @@ __device__ RowInfo row_info(const PanelArgs& a, int64_t r, uint32_t* bucket) {
   const double* s0 = a.scr + cy * a.nx + cx;
   const double pwv = (1.0 - wx) * (1.0 - wy) * s0[0] + wx * (1.0 - wy) * s0[1] +
                      (1.0 - wx) * wy * s0[a.nx] + wx * wy * s0[a.nx + 1];
-  if (ox || oy) atomicAdd(&a.counters[0], 1ull);
-  if (a.pwv_out) a.pwv_out[(int64_t)p * a.out_ld + (n - a.out_t0)] = (float)pwv;
+  if (first && (ox || oy)) atomicAdd(&a.counters[0], 1ull);
+  if (first && a.pwv_out) a.pwv_out[(int64_t)p * a.out_ld + (n - a.out_t0)] = (float)pwv;
   int64_t li;
   double lw;
   bool ol;
   clamp_cell((pwv - a.pwv0) / a.dpwv, a.n_pwv, &li, &lw, &ol);
-  if (ol) atomicAdd(&a.counters[1], 1ull);
+  if (first && ol) atomicAdd(&a.counters[1], 1ull);
   q.li = (int)li;
   q.lw = (float)lw;
   const double el = th + a.theta0 + a.dtheta[p];
   const double se = sin(el);
   // an elevation outside (0, pi) has no airmass (only a user trajectory
   // can reach one: analytic scans are checked before launch)
-  if (!(se > 0.0)) atomicAdd(&a.counters[2], 1ull);
+  if (first && !(se > 0.0)) atomicAdd(&a.counters[2], 1ull);
   q.csc = (float)(1.0 / se);
   q.src = 0;
   if (a.cube) {
@@ -104,8 +115,11 @@ __device__ RowInfo row_info(const PanelArgs& a, int64_t r, uint32_t* bucket) {
       clamp_cell(ga, a.n_az, &ca, &wa, &d0);
       clamp_cell(ge, a.n_el, &ce, &we, &d1);
       q.src = 1;
-      q.wa = (float)wa;
-      q.we = (float)we;
+      const float fa = (float)wa, fe = (float)we;
+      q.w[0] = (1.f - fa) * (1.f - fe);
+      q.w[1] = fa * (1.f - fe);
+      q.w[2] = (1.f - fa) * fe;
+      q.w[3] = fa * fe;
       q.sbase = (ce * a.n_az + ca) * a.cube_ld;
       if (a.n_buckets > 1)
         *bucket = (uint32_t)((ce >> a.cell_shift) * a.n_az_coarse + (ca >> a.cell_shift));
@@ -114,87 +128,191 @@ __device__ RowInfo row_info(const PanelArgs& a, int64_t r, uint32_t* bucket) {
   return q;
 }
 
-// dP of kPanelRows rows (records in LDS) over every bin; rows[rr] is the
-// panel row record rr goes to.  The table and cube reads of 8 rows are
-// issued together before their arithmetic (addresses clamped into the
-// arrays, so rows without data read harmless values that are not used),
-// which keeps 48 loads per lane in flight instead of one row's.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+// the same with the alignment of a float (a cube's rows may have any pitch)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+constexpr int kTileBins = 4 * 256;   // bins of a workgroup pass, 4 per lane
+
+// 1 - e^-x for x >= 0 to about one ulp: n = rint(-x log2 e), r = -x - n ln 2
+// in two parts, e^r - 1 = r + r^2 p(r) with p fitted on |r| <= ln(2) / 2 for
+// the relative error of e^r - 1 (2e-9), and 1 - e^-x = (1 - 2^n) - 2^n (e^r -
+// 1).  15 instructions where the library's expm1f takes 24; beyond x = 40
+// the result is 1 either way.
+__device__ __forceinline__ float one_minus_exp(float x) {
+  const float y = __builtin_elementwise_minimum(x, 40.f);   // keeps a NaN
+  constexpr float kMagic = 12582912.f;   // 1.5 * 2^23: the sum's low bits are n
+  const float t = __builtin_fmaf(y, -1.44269504088896341f, kMagic);
+  const float n = t - kMagic;
+  float r = __builtin_fmaf(n, -0.693145751953125f, -y);
+  r = __builtin_fmaf(n, -1.428606765330187045e-6f, r);
+  float p = 1.98458888917230070e-4f;
+  p = __builtin_fmaf(p, r, 1.39406265225261450e-3f);
+  p = __builtin_fmaf(p, r, 8.33338964730501175e-3f);
+  p = __builtin_fmaf(p, r, 4.16663624346256256e-2f);
+  p = __builtin_fmaf(p, r, 1.66666656732559204e-1f);
+  p = __builtin_fmaf(p, r, 0.5f);
+  const float q = __builtin_fmaf(r * r, p, r);
+  const float s = __builtin_bit_cast(float, (__builtin_bit_cast(uint32_t, t) << 23) + 0x3f800000u);
+  return __builtin_fmaf(-s, q, 1.f - s);
+}
+
 // Counts (range counter 3) the (row, bin) elements whose deviation from
 // the reference spectrum exceeds P / 8.  While none does, the terms of
 // sum_j |dP_j| B_jk add up to at most P_KID / 8 (B >= 0, P > 0), so the
 // 16-bit operands of the split contraction (relative error 2^-17 on each
 // term) stay within 1e-6 of P_KID; beyond it the stated tolerance of the
 // reference-row contraction is not guaranteed.
+// far is the wave's count.
 __device__ __forceinline__ void far_from_reference(const PanelArgs& a, uint32_t far) {
-  if (far) atomicAdd(&a.counters[3], (unsigned long long)far);
+  if (far && (threadIdx.x & 63) == 0) atomicAdd(&a.counters[3], (unsigned long long)far);
 }
 
-__device__ __forceinline__ void panel_rows(const PanelArgs& a, const RowInfo* ri,
-                                           const int64_t* rows) {
-  constexpr int kB = 8;
-  const int64_t Fp = a.Fp;
-  const bool with_cube = a.cube != nullptr;
-  const int64_t ld = a.cube_ld, crow = (int64_t)a.n_az * a.cube_ld;
-  uint32_t far = 0;   // elements with |dP| > P / 8 (see far_from_reference)
-  for (int j = threadIdx.x; j < a.Fp; j += blockDim.x) {
-    const bool inF = j < a.F;
-    const int jj = inF ? j : a.F - 1;
-    const float E = a.E[j], D = a.D[j], W = a.W[j], Pr = a.Pref[j];
-#pragma unroll 1
-    for (int rb = 0; rb < kPanelRows; rb += kB) {
-      float t0[kB], t1[kB], cs[kB][4];
+// The bins of one workgroup pass: this lane's 4 bins from j, of which those
+// below F exist (the spectra are zero beyond).
+struct Bins {
+  f32x4 E, D, W, Pr;
+  uint32_t j, js;        // first bin; first bin of a cube load
+  __device__ Bins(const PanelArgs& a, uint32_t j0) : j(j0) {
+    const bool in = j < (uint32_t)a.Fp;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    E = in ? *reinterpret_cast<const f32x4*>(a.E + j) : zero;
+    D = in ? *reinterpret_cast<const f32x4*>(a.D + j) : zero;
+    W = in ? *reinterpret_cast<const f32x4*>(a.W + j) : zero;
+    Pr = in ? *reinterpret_cast<const f32x4*>(a.Pref + j) : zero;
+    js = min(j, (uint32_t)max(a.F - 4, 0));
+  }
+  // p[j .. j + 3], zero past the last bin; p is a row of F floats, of any
+  // alignment.  The lane across the end reads the row's last four floats
+  // and shifts them.
+  __device__ __forceinline__ f32x4 cube(const float* p, int F) const {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (F < 4) {
+      for (int k = 0; k < 4; ++k)
+        if ((int)j + k < F) v[k] = p[j + k];
+      return v;
+    }
+    v = *reinterpret_cast<const f32x4u*>(p + js);
+    if (js != j) {
+      const uint32_t s = j - js;
+      v[0] = s == 1 ? v[1] : s == 2 ? v[2] : s == 3 ? v[3] : 0.f;
+      v[1] = s == 1 ? v[2] : s == 2 ? v[3] : 0.f;
+      v[2] = s == 1 ? v[3] : 0.f;
+      v[3] = 0.f;
+    }
+    return v;
+  }
+};
+
+// dP of a row: t0, t1 the table rows around its PWV, ps the source power.
+__device__ __forceinline__ f32x4 row_deviation(const Bins& b, f32x4 t0, f32x4 t1, f32x4 ps,
+                                               float lw, float csc, bool src, uint32_t* far) {
+  f32x4 dP;
 #pragma unroll
-      for (int u = 0; u < kB; ++u) {
-        const RowInfo& q = ri[rb + u];
-        t0[u] = a.tau[(int64_t)q.li * Fp + jj];
-        t1[u] = a.tau[(int64_t)(q.li + 1) * Fp + jj];
-        if (with_cube) {
-          const float* c = a.cube + q.sbase + jj;
-          cs[u][0] = c[0];
-          cs[u][1] = c[ld];
-          cs[u][2] = c[crow];
-          cs[u][3] = c[crow + ld];
-        }
+  for (int k = 0; k < 4; ++k) {
+    const float tz = (1.f - lw) * t0[k] + lw * t1[k];
+    const float xi = one_minus_exp(csc * tz);
+    float P = b.E[k] + xi * b.D[k];
+    if (src) P += (1.f - xi) * (b.W[k] * ps[k]);
+    dP[k] = P - b.Pr[k];
+    *far += (uint32_t)__builtin_popcountll(__ballot(fabsf(dP[k]) > 0.125f * P));
+  }
+  return dP;
+}
+
+// Rows of one workgroup, record(rr) giving the record and panel row of the
+// rr-th, over the passes of 1024 bins first, first + stride, ...  Within a
+// pass the spectra E, D, W, Pref stay in registers, and the cube corners
+// are loaded only where a row's cell is another than the row's before.
+// kBatch rows' table values are loaded together, ahead of their arithmetic.
+template <class Rec>
+__device__ __forceinline__ void panel_rows(const PanelArgs& a, int n_rows, int first,
+                                           int stride, Rec record) {
+  constexpr int kBatch = 2;
+  const int64_t Fp = a.Fp;
+  const int64_t ld = a.cube_ld, crow = (int64_t)a.n_az * a.cube_ld;
+  uint32_t far = 0;
+  for (int j0 = first * kTileBins; j0 < a.Fp; j0 += stride * kTileBins) {
+    const Bins b(a, j0 + 4 * threadIdx.x);
+    const bool in = b.j < (uint32_t)a.Fp;
+    const uint32_t jc = in ? b.j : 0;
+    int64_t cell = -1;                 // the corners held in c
+    f32x4 c[4] = {};
+#pragma unroll 1
+    for (int rb = 0; rb < n_rows; rb += kBatch) {
+      RowInfo q[kBatch];
+      float* out[kBatch];
+      f32x4 t0[kBatch], t1[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        int64_t row;
+        q[u] = record(rb + u, &row);
+        out[u] = a.panel + row * Fp;
+        const float* tr = a.tau + (int64_t)q[u].li * Fp + jc;
+        t0[u] = *reinterpret_cast<const f32x4*>(tr);
+        t1[u] = *reinterpret_cast<const f32x4*>(tr + Fp);
       }
 #pragma unroll
-      for (int u = 0; u < kB; ++u) {
-        const RowInfo& q = ri[rb + u];
-        float dP = 0.f;
-        if (q.valid && inF) {
-          const float tz = (1.f - q.lw) * t0[u] + q.lw * t1[u];
-          const float xi = -expm1f(-q.csc * tz);
-          float P = E + xi * D;
-          if (q.src) {
-            const float ps = (1.f - q.wa) * (1.f - q.we) * cs[u][0] +
-                             q.wa * (1.f - q.we) * cs[u][1] +
-                             (1.f - q.wa) * q.we * cs[u][2] + q.wa * q.we * cs[u][3];
-            P += (1.f - xi) * (W * ps);
+      for (int u = 0; u < kBatch; ++u) {
+        const bool src = q[u].valid && q[u].src;
+        f32x4 ps = {0.f, 0.f, 0.f, 0.f};
+        if (src) {
+          if (q[u].sbase != cell) {
+            cell = q[u].sbase;
+            const float* p = a.cube + cell;
+            c[0] = b.cube(p, a.F);
+            c[1] = b.cube(p + ld, a.F);
+            c[2] = b.cube(p + crow, a.F);
+            c[3] = b.cube(p + crow + ld, a.F);
           }
-          dP = P - Pr;
-          far += fabsf(dP) > 0.125f * P;
+          ps = q[u].w[0] * c[0] + q[u].w[1] * c[1] + q[u].w[2] * c[2] + q[u].w[3] * c[3];
         }
-        a.panel[rows[rb + u] * Fp + j] = dP;
+        f32x4 dP = {0.f, 0.f, 0.f, 0.f};
+        if (q[u].valid)
+          dP = row_deviation(b, t0[u], t1[u], ps, q[u].lw, q[u].csc, src, &far);
+        // past the caches: the panel is larger than them, and what it would
+        // push out (table rows, cube corners) is read again
+        if (in) __builtin_nontemporal_store(dP, reinterpret_cast<f32x4*>(out[u] + b.j));
       }
     }
   }
   far_from_reference(a, far);
 }
 
+// A wave-uniform value, in a scalar register.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ float uniform(float v) {
+  return __builtin_bit_cast(float, uniform(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ int64_t uniform(int64_t v) {
+  return ((int64_t)uniform((int)(v >> 32)) << 32) | (uint32_t)uniform((int)v);
+}
+
 }  // namespace
 
-// Unsorted panel: workgroup b computes rows 32 b .. 32 b + 31 (one pixel,
-// consecutive samples); the first 32 threads derive the row records.
+// Rows in their own order: workgroup (b, y) computes rows R b .. R b + R - 1
+// (one pixel, consecutive samples), R = a.rows_wg, in the bin passes y, y +
+// gridDim.y, ...; the first R threads derive the row records.
 __global__ __launch_bounds__(256) void k_panel(PanelArgs a) {
   __shared__ RowInfo ri[kPanelRows];
-  __shared__ int64_t rows[kPanelRows];
-  const int64_t row0 = (int64_t)blockIdx.x * kPanelRows;
-  if (threadIdx.x < kPanelRows) {
+  const int64_t row0 = (int64_t)blockIdx.x * a.rows_wg;
+  if ((int)threadIdx.x < a.rows_wg) {
     uint32_t bucket;
-    ri[threadIdx.x] = row_info(a, row0 + threadIdx.x, &bucket);
-    rows[threadIdx.x] = row0 + threadIdx.x;
+    ri[threadIdx.x] = row_info(a, row0 + threadIdx.x, &bucket, blockIdx.y == 0);
   }
   __syncthreads();
-  panel_rows(a, ri, rows);
+  panel_rows(a, a.rows_wg, blockIdx.y, gridDim.y, [&](int rr, int64_t* row) {
+    *row = row0 + rr;
+    RowInfo q = ri[rr];
+    q.valid = uniform(q.valid);
+    q.src = uniform(q.src);
+    q.li = uniform(q.li);
+    q.sbase = uniform(q.sbase);
+    q.lw = uniform(q.lw);
+    q.csc = uniform(q.csc);
+    for (int k = 0; k < 4; ++k) q.w[k] = uniform(q.w[k]);
+    return q;
+  });
 }
 
 // hist[bucket] += 1 for every active lane; returns the lane's old value.
@@ -221,7 +339,7 @@ __global__ __launch_bounds__(256) void k_panel_info(PanelArgs a) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= (int64_t)a.n_pix * a.Tpad) return;
   uint32_t bucket;
-  const RowInfo q = row_info(a, r, &bucket);
+  const RowInfo q = row_info(a, r, &bucket, true);
   reinterpret_cast<RowInfo*>(a.rinfo)[r] = q;
   a.key[r] = bucket;
   bucket_add(a.hist, bucket, (uint32_t)(a.n_buckets - 1));
@@ -259,110 +377,28 @@ __global__ __launch_bounds__(256) void k_panel_scatter(PanelArgs a) {
   a.order[pos] = (uint32_t)r;
 }
 
-// *(base + boff bytes): a scalar base plus a 32-bit lane offset, which
-// the load takes as its address operands directly.
-__device__ __forceinline__ float at_byte(const float* base, uint32_t boff) {
-  return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + boff);
-}
-
-// Step 4: workgroup b computes the 32 rows at positions 32 b .. 32 b + 31
-// of the bucket order, 4 rows at a time over all bins.
-// The order slots and row records are read at workgroup-uniform
-// addresses, so they load into scalar registers and each row's table,
-// cube and panel base address is a scalar value: an access costs the
-// lane's bin offset only.  The table and cube reads of a batch are issued
-// before its arithmetic.  Rows in bucket order mostly read the same cube
-// corners as their neighbours, and often the same table rows: such a row
-// takes the values its neighbour loaded, and a row without data loads
-// nothing.  The arithmetic per (row, bin) is that of panel_rows.
-// Six workgroups per CU as the occupancy target: the compiler then keeps
-// the kernel at 72 VGPRs (seven waves per SIMD, against five at its
-// unconstrained 85), which hides more of the table and cube load latency.
-__global__ __launch_bounds__(256, 6) void k_panel_sorted(PanelArgs a) {
-  uint32_t far = 0;   // elements with |dP| > P / 8 (see far_from_reference)
-  constexpr int kB = 4;   // rows per batch (scalar registers)
-  const RowInfo* __restrict__ rinfo = reinterpret_cast<const RowInfo*>(a.rinfo);
-  const uint32_t* ord = a.order + (int64_t)blockIdx.x * kPanelRows;
-  const int64_t Fp = a.Fp;
-  const uint32_t F = (uint32_t)a.F;
-  const int64_t crow = (int64_t)a.n_az * a.cube_ld;
-  const uint32_t row_b = 4u * (uint32_t)Fp;          // next table row, bytes
-  const uint32_t az_b = 4u * (uint32_t)a.cube_ld;    // next azimuth cell, bytes
-#pragma unroll 1
-  for (int rb = 0; rb < kPanelRows; rb += kB) {
-    RowInfo q[kB];
-    const float* tr[kB];   // table row below the PWV
-    const float* c0[kB];   // cube corners (el, az) and (el, az + 1)
-    const float* c1[kB];   // cube corners (el + 1, az) and (el + 1, az + 1)
-    float* out[kB];
-#pragma unroll
-    for (int u = 0; u < kB; ++u) {
-      const uint32_t r = ord[rb + u];
-      q[u] = rinfo[r];
-      tr[u] = a.tau + (int64_t)q[u].li * Fp;
-      c0[u] = a.cube + q[u].sbase;
-      c1[u] = c0[u] + crow;
-      out[u] = a.panel + (int64_t)r * Fp;
-    }
-    for (uint32_t j = threadIdx.x; j < (uint32_t)Fp; j += blockDim.x) {
-      const bool inF = j < F;
-      // byte offsets of the bin, added to the scalar base addresses
-      const uint32_t jb = 4u * j;
-      const uint32_t jjb = 4u * (inF ? j : F - 1);
-      const float E = at_byte(a.E, jb), D = at_byte(a.D, jb);
-      const float W = at_byte(a.W, jb), Pr = at_byte(a.Pref, jb);
-      float t0[kB], t1[kB], cs[kB][4];
-#pragma unroll
-      for (int u = 0; u < kB; ++u) {
-        // uniform branches: skip rows without data, reuse a neighbour's
-        // values where the addresses are the same
-        const bool nt = q[u].valid;
-        const bool nc = q[u].valid && q[u].src;
-        if (!nt) {
-          t0[u] = t1[u] = 0.f;
-        } else if (u > 0 && q[u - 1].valid && q[u].li == q[u - 1].li) {
-          t0[u] = t0[u - 1];
-          t1[u] = t1[u - 1];
-        } else {
-          t0[u] = at_byte(tr[u], jjb);
-          t1[u] = at_byte(tr[u], jjb + row_b);
-        }
-        if (!nc) {
-#pragma unroll
-          for (int m = 0; m < 4; ++m) cs[u][m] = 0.f;
-        } else if (u > 0 && q[u - 1].valid && q[u - 1].src &&
-                   q[u].sbase == q[u - 1].sbase) {
-#pragma unroll
-          for (int m = 0; m < 4; ++m) cs[u][m] = cs[u - 1][m];
-        } else {
-          cs[u][0] = at_byte(c0[u], jjb);
-          cs[u][1] = at_byte(c0[u], jjb + az_b);
-          cs[u][2] = at_byte(c1[u], jjb);
-          cs[u][3] = at_byte(c1[u], jjb + az_b);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kB; ++u) {
-        float dP = 0.f;
-        if (q[u].valid && inF) {
-          const float tz = (1.f - q[u].lw) * t0[u] + q[u].lw * t1[u];
-          const float xi = -expm1f(-q[u].csc * tz);
-          float P = E + xi * D;
-          if (q[u].src) {
-            const float ps = (1.f - q[u].wa) * (1.f - q[u].we) * cs[u][0] +
-                             q[u].wa * (1.f - q[u].we) * cs[u][1] +
-                             (1.f - q[u].wa) * q[u].we * cs[u][2] +
-                             q[u].wa * q[u].we * cs[u][3];
-            P += (1.f - xi) * (W * ps);
-          }
-          dP = P - Pr;
-          far += fabsf(dP) > 0.125f * P;
-        }
-        *reinterpret_cast<float*>(reinterpret_cast<char*>(out[u]) + jb) = dP;
-      }
-    }
-  }
-  far_from_reference(a, far);
+// Step 4: workgroup (b, y) computes the rows at positions R b .. R b + R -
+// 1 of the bucket order.  The order slots and row records are read through
+// the constant address space at workgroup-uniform addresses, so they load
+// into scalar registers: every address and branch of a row is scalar.
+__global__ __launch_bounds__(256) void k_panel_sorted(PanelArgs a) {
+  typedef const __attribute__((address_space(4))) uint32_t* CU32;
+  typedef const __attribute__((address_space(4))) RowInfo* CRow;
+  const CU32 ord = (CU32)(uintptr_t)(a.order + (int64_t)blockIdx.x * a.rows_wg);
+  const CRow rinfo = (CRow)(uintptr_t)a.rinfo;
+  panel_rows(a, a.rows_wg, blockIdx.y, gridDim.y, [&](int rr, int64_t* row) {
+    const uint32_t r = ord[rr];
+    *row = r;
+    RowInfo q;
+    q.valid = rinfo[r].valid;
+    q.li = rinfo[r].li;
+    q.lw = rinfo[r].lw;
+    q.csc = rinfo[r].csc;
+    q.src = rinfo[r].src;
+    for (int k = 0; k < 4; ++k) q.w[k] = rinfo[r].w[k];
+    q.sbase = rinfo[r].sbase;
+    return q;
+  });
 }
 
 __global__ void k_fill_u32(uint32_t* p, int n, uint32_t v) {
@@ -370,11 +406,15 @@ __global__ void k_fill_u32(uint32_t* p, int n, uint32_t v) {
   if (i < n) p[i] = v;
 }
 
-void launch_panel(const PanelArgs& a, hipStream_t s) {
+void launch_panel(const PanelArgs& a0, hipStream_t s) {
+  PanelArgs a = a0;
   const int64_t rows = (int64_t)a.n_pix * a.Tpad;
-  const int64_t blocks = rows / kPanelRows;
+  const int passes = (a.Fp + kTileBins - 1) / kTileBins;
+  // few rows: fewer of them per workgroup, and a workgroup per bin pass
+  a.rows_wg = rows >= 1024 * kPanelRows ? kPanelRows : 8;
+  const dim3 grid((unsigned)(rows / a.rows_wg), rows >= 1024 * kPanelRows ? 1 : passes);
   if (a.n_buckets <= 1) {
-    hipLaunchKernelGGL(k_panel, dim3((unsigned)blocks), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_panel, grid, dim3(256), 0, s, a);
     return;
   }
   const unsigned rb = (unsigned)((rows + 255) / 256);
@@ -383,7 +423,7 @@ void launch_panel(const PanelArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_panel_info, dim3(rb), dim3(256), 0, s, a);
   hipLaunchKernelGGL(k_panel_scan, dim3(1), dim3(1024), 0, s, a.hist, a.n_buckets);
   hipLaunchKernelGGL(k_panel_scatter, dim3(rb), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(k_panel_sorted, dim3((unsigned)blocks), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_panel_sorted, grid, dim3(256), 0, s, a);
 }
 
 }  // namespace gtod

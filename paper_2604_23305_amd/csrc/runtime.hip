@@ -357,11 +357,12 @@ gtod_status plan_chunks(gtod_ctx* c, JobPlan* pl, int idx, size_t panel_bytes,
     pl->pink_per = per;
     return GTOD_OK;
   }
-  // with a source cube the rows are bucketed by coarse cube cell (at most
-  // kPanelMaxBuckets cells); each row then also needs a record, a key and
-  // an order slot beside its panel row
+  // with a source cube (and rows enough, see kPanelSortRows) the rows are
+  // bucketed by coarse cube cell (at most kPanelMaxBuckets cells); each row
+  // then also needs a record, a key and an order slot beside its panel row
   int n_buckets = 1, cell_shift = 0, n_az_c = 0;
-  if (j.cube) {
+  if (j.cube && j.scan_kind != GTOD_SCAN_STARE &&
+      (int64_t)j.n_pix * (j.t_end - j.t_begin) >= kPanelSortRows) {
     for (;; ++cell_shift) {
       const int64_t ne = ((int64_t)j.n_el + (1 << cell_shift) - 1) >> cell_shift;
       const int64_t na = ((int64_t)j.n_az + (1 << cell_shift) - 1) >> cell_shift;

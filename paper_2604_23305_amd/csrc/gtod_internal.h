@@ -244,15 +244,15 @@ struct ScreenConvArgs {
   int64_t nx, ny;
   int rx, ry;                // footprint half widths in cells
   double dx, dy, r_tel, t_edge_db;
-  double* w;                 // [2ry+1][2rx+1] scratch: normalised weights
+  double* w;                 // scratch: factors of the weights, row widths
+  int strip;                 // output rows per workgroup (set by the launcher)
 };
-constexpr int kScreenTileX = 64, kScreenTileY = 32, kMaxFootprint = 32;
+constexpr int kMaxFootprint = 32;
 constexpr int kMaxSrcNodes = 20000;   // n_az n_el of a source grid
 void launch_gauss_legendre(double* x, double* w, int n, hipStream_t s);
 void launch_beam_table(const BeamArgs& a, hipStream_t s);
 int launch_source_conv(const SrcConvArgs& a, hipStream_t s);   // 0 ok
-void launch_screen_weights(const ScreenConvArgs& a, hipStream_t s);
-int launch_screen_conv(const ScreenConvArgs& a, hipStream_t s); // 0 ok
+void launch_screen_conv(const ScreenConvArgs& a, hipStream_t s);
 
 // Context services for library parts outside the runtime file: device
 // memory charged to the context's budget, the error message, and a few

@@ -17,7 +17,8 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libgtod.so")
 
 SOURCES = ["runtime.hip", "k_setup.hip", "k_panel.hip", "k_gemm.hip",
-           "k_pink.hip", "k_skydip.hip", "k_reduce.hip", "k_inputs.hip", "sink.hip"]
+           "k_pink.hip", "k_skydip.hip", "k_reduce.hip", "k_inputs.hip", "k_source.hip",
+           "sink.hip"]
 
 HIPFLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",
             "-ffp-contract=fast", "-Wall", "-Wno-unused-function",

@@ -229,7 +229,10 @@ struct BeamArgs {
   int F, n_a, n_b;
   double da, db;             // grid spacings (rad) along a and b
   float* table;              // [F][n_b][n_a] peak-normalised far field
+  int panels;                // unit panels of 2 pi rho R / lambda
+  double* poly;              // [panels][kBeamTerms] scratch: H / H(0)
 };
+constexpr int kBeamTerms = 13;
 struct SrcConvArgs {
   const float* in;           // [n_el][n_az][ld_in] specific intensity
   int64_t ld_in, ld_out;
@@ -237,7 +240,20 @@ struct SrcConvArgs {
   double el0, del, scale;    // scale = A_p daz del
   const float* table;        // [nf][n_el][n_az] far field of the batch
   float* out;                // [n_el][n_az][ld_out]
+  // scratch of the transforms
+  int log_x, log_y;          // padded sizes 2^log of az and el
+  const double2* twiddles;   // [2^kMaxFftLog]
+  float* planes;             // [nf][n_el][n_az] intensities times cos(el)
+  float* powers;             // [nf][n_el][n_az]
+  double2* spectrum;         // [nf][2^log_x / 2 + 1][n_el]
+  double* rows_table;        // [nf][2^log_x / 2 + 1][n_el]
+  double* norms;             // [nf][2][row groups] squared 2-norms, in parts
 };
+constexpr int kMinFftLog = 5, kMaxFftLog = 9;
+// Outputs below this part of the product of the 2-norms are summed directly:
+// the transforms' error, at most 2^-51 of it, is then at most 2^-26 of the
+// output.
+constexpr double kSrcLeast = 0x1p-25;
 struct ScreenConvArgs {
   const double* in;          // [ny][nx]
   double* out;
@@ -252,6 +268,12 @@ constexpr int kMaxSrcNodes = 20000;   // n_az n_el of a source grid
 void launch_gauss_legendre(double* x, double* w, int n, hipStream_t s);
 void launch_beam_table(const BeamArgs& a, hipStream_t s);
 int launch_source_conv(const SrcConvArgs& a, hipStream_t s);   // 0 ok
+void launch_beam_polynomials(const BeamArgs& a, hipStream_t s);
+void launch_beam_eval(const BeamArgs& a, hipStream_t s);
+void launch_src_twiddles(double2* tw, hipStream_t s);
+int src_fft_log(int n);
+int src_fft_norms(int n_az, int n_el);
+int launch_source_fft(const SrcConvArgs& a, hipStream_t s);    // 0 ok
 void launch_screen_conv(const ScreenConvArgs& a, hipStream_t s);
 
 // Context services for library parts outside the runtime file: device

@@ -9,10 +9,11 @@
 // evaluated with Gauss-Legendre quadrature on [0, R] (the node count is
 // chosen by the runtime from the largest 2 pi rho R / lambda of the grid).
 // Source: P(i, j) = A_p daz del sum_{i', j'} I(i', j') cos(el_j') F(rho),
-// rho = sqrt(((i - i') daz)^2 + ((j - j') del)^2): one block per (frequency,
-// 32x32 output tile) holding the frequency's weighted intensity plane and
-// its far-field table F[|dj|][|di|] in LDS; each thread sums 2x2 outputs
-// in FP64.  Screen: weights A(r) normalised to 1 over the cells within R,
+// rho = sqrt(((i - i') daz)^2 + ((j - j') del)^2).  Small and very long grids,
+// summed directly here (the others by transforms, in k_source.hip): one block
+// per (frequency, 32x32 output tile) holding the frequency's weighted intensity
+// plane and its far-field table F[|dj|][|di|] in LDS; each thread sums 2x2
+// outputs in FP64.  Screen: weights A(r) normalised to 1 over the cells within R,
 // edges clamped; A is a product of a function of x and one of y inside the
 // disk, so a row's cells are summed once per row of the footprint.
 #include <hip/hip_runtime.h>
@@ -60,7 +61,8 @@ __global__ void k_gauss_legendre(double* x, double* w, int n) {
   w[i] = 1.0 / ((1.0 - z * z) * dp * dp);
 }
 
-// One thread per (a, b, frequency).
+// One thread per (a, b, frequency), a quadrature each: for calls of few
+// entries (the others from polynomials, in k_source.hip).
 __global__ __launch_bounds__(256) void k_beam_table(BeamArgs a) {
   const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t per = (int64_t)a.n_a * a.n_b;
@@ -108,12 +110,12 @@ __global__ __launch_bounds__(256) void k_source_conv(SrcConvArgs a) {
     const float* rF0 = sF + min(abs(j0_ - jp), a.n_el - 1) * a.n_az;
     const float* rF1 = sF + min(abs(j1 - jp), a.n_el - 1) * a.n_az;
     for (int ip = 0; ip < a.n_az; ++ip) {
-      const float v = rI[ip];
+      const double v = rI[ip];
       const int e0 = min(abs(i0 - ip), a.n_az - 1), e1 = min(abs(i1 - ip), a.n_az - 1);
-      acc00 += (double)(v * rF0[e0]);
-      acc01 += (double)(v * rF0[e1]);
-      acc10 += (double)(v * rF1[e0]);
-      acc11 += (double)(v * rF1[e1]);
+      acc00 = fma(v, (double)rF0[e0], acc00);
+      acc01 = fma(v, (double)rF0[e1], acc01);
+      acc10 = fma(v, (double)rF1[e0], acc10);
+      acc11 = fma(v, (double)rF1[e1], acc11);
     }
   }
   auto put = [&](int i, int j, double acc) {

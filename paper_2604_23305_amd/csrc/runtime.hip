@@ -1354,6 +1354,26 @@ namespace {
 // J0 is kr = 2 pi rho_max R / lambda_min.
 int beam_nodes(double kr) { return (int)round_up((int64_t)std::ceil(0.6 * kr) + 64, 32); }
 
+// Unit panels of the far field's polynomials, or 0: every entry by its own
+// quadrature, where the 13 quadratures of each panel would be about as many
+// (9 x 7 x 4 entries: 67 us either way; 121 x 121 x 3000: 31.9 and 0.22 ms).
+int beam_panels(double kr, int64_t entries) {
+  const int64_t n = (int64_t)kr + 2;
+  return entries > 16 * n ? (int)n : 0;
+}
+// Source grids convolved by transforms: whose padded sides fit a workgroup's
+// transform, and from where their seven launches and the padding cost less
+// than the direct sums (3000 frequencies, us direct / transformed: 16 x 16
+// 220 / -, 25 x 25 433 / 465, 32 x 32 638 / 469, 40 x 40 3032 / 745; 100
+// frequencies: 25 x 25 120 / 125, 32 x 32 149 / 126, 121 x 121 6593 / 210).
+bool src_fft(int n_az, int n_el) {
+  return n_az * n_el >= 700 && std::max(n_az, n_el) * 2 - 1 <= 1 << kMaxFftLog;
+}
+// Frequencies of a batch: their planes (0.55 MB each at 121 x 121) stay near
+// the last-level cache's size, and a launch still fills the card.
+constexpr int64_t kSrcBatch = 512;
+size_t beam_poly_bytes(int panels) { return (size_t)round_up((int64_t)panels * kBeamTerms * 8, 256); }
+
 // Stages nu (host [F]) through the stream's pinned ring; returns the device
 // copy, valid for work enqueued on s before the slot's next reuse.
 gtod_status stage_doubles(gtod_ctx* c, StreamWs* w, hipStream_t s, const double* h,
@@ -1419,8 +1439,17 @@ gtod_status gtod_far_field(gtod_ctx* c, const double* nu_hz, int32_t F, int32_t 
   b.db = db;
   b.table = out;
   launch_gauss_legendre(b.gl_x, b.gl_w, b.n_nodes, s);
-  timed(c, GTOD_KERNEL_BEAM, (double)n_a * n_b * F * b.n_nodes, s,
-        [&] { launch_beam_table(b, s); });
+  b.poly = b.gl_w + b.n_nodes;
+  b.panels = beam_panels(kr, (int64_t)n_a * n_b * F);
+  if ((size_t)b.n_nodes * 16 + beam_poly_bytes(b.panels) > w->panel_bytes) b.panels = 0;
+  timed(c, GTOD_KERNEL_BEAM, (double)n_a * n_b * F * b.n_nodes, s, [&] {
+    if (b.panels) {
+      launch_beam_polynomials(b, s);
+      launch_beam_eval(b, s);
+    } else {
+      launch_beam_table(b, s);
+    }
+  });
   HIP_TRY(c, hipGetLastError());
   HIP_TRY(c, hipEventRecord(w->ev[slot], s));
   w->ev_used[slot] = true;
@@ -1461,17 +1490,45 @@ gtod_status gtod_convolve_source(gtod_ctx* c, const float* in, int32_t n_az, int
   b.n_nodes = beam_nodes(kr);
   b.gl_x = (double*)w->panel;
   b.gl_w = b.gl_x + b.n_nodes;
-  const int64_t head = round_up((int64_t)b.n_nodes * 16, 256);
-  const int64_t nf_max = ((int64_t)w->panel_bytes - head) / (nn * 4);
+  // workspace: the quadrature, the polynomials, then per frequency the table
+  // and the transforms' planes; what does not fit is done without
+  int64_t head = round_up((int64_t)b.n_nodes * 16, 256);
+  int64_t nf_max = ((int64_t)w->panel_bytes - head) / (nn * 4);
   if (nf_max < 1) return fail(c, GTOD_EINVAL, "workspace too small for one far-field table");
+  char* const ws = (char*)w->panel;
+  b.panels = beam_panels(kr, nn * F);
+  b.poly = (double*)(ws + head);
+  const int64_t poly = (int64_t)beam_poly_bytes(b.panels);
+  const int64_t left = (int64_t)w->panel_bytes - head - poly;
+  if (left < nn * 4) {
+    b.panels = 0;
+  } else {
+    head += poly;
+    nf_max = left / (nn * 4);
+  }
+  SrcConvArgs v{};
+  bool fft = src_fft(n_az, n_el);
+  int64_t spec = 0, norms = 0;
+  if (fft) {
+    v.log_x = src_fft_log(n_az);
+    v.log_y = src_fft_log(n_el);
+    spec = (((int64_t)1 << v.log_x) / 2 + 1) * n_el;
+    norms = src_fft_norms(n_az, n_el);
+    const int64_t twiddles = (int64_t)16 << kMaxFftLog;
+    const int64_t n = ((int64_t)w->panel_bytes - head - twiddles) / (spec * 24 + norms * 8 + nn * 12);
+    fft = n >= 1;
+    if (fft) {
+      nf_max = std::min(n, kSrcBatch);
+      v.twiddles = (const double2*)(ws + head);
+      head += twiddles;
+    }
+  }
   b.r_tel = r_tel;
   b.t_edge_db = t_edge_db;
   b.n_a = n_az;
   b.n_b = n_el;
   b.da = daz;
   b.db = del;
-  b.table = (float*)((char*)w->panel + head);
-  SrcConvArgs v{};
   v.in = in;
   v.ld_in = ld_in;
   v.ld_out = ld_out;
@@ -1480,19 +1537,37 @@ gtod_status gtod_convolve_source(gtod_ctx* c, const float* in, int32_t n_az, int
   v.el0 = el0;
   v.del = del;
   v.scale = M_PI * r_tel * r_tel * daz * del;
-  v.table = b.table;
   v.out = out;
+  if (fft) {
+    v.spectrum = (double2*)(ws + head);
+    v.rows_table = (double*)(v.spectrum + spec * nf_max);
+    v.norms = v.rows_table + spec * nf_max;
+    b.table = (float*)(v.norms + norms * nf_max);
+    v.planes = b.table + nn * nf_max;
+    v.powers = v.planes + nn * nf_max;
+    launch_src_twiddles((double2*)v.twiddles, s);
+  } else {
+    b.table = (float*)(ws + head);
+  }
+  v.table = b.table;
   launch_gauss_legendre(b.gl_x, b.gl_w, b.n_nodes, s);
   for (int f0 = 0; f0 < F; f0 += (int)nf_max) {
     const int nf = (int)std::min<int64_t>(nf_max, F - f0);
     b.nu = d_nu + f0;
     b.F = nf;
-    timed(c, GTOD_KERNEL_BEAM, (double)nn * nf * b.n_nodes, s, [&] { launch_beam_table(b, s); });
+    timed(c, GTOD_KERNEL_BEAM, (double)nn * nf * b.n_nodes, s, [&] {
+      if (b.panels) {
+        if (f0 == 0) launch_beam_polynomials(b, s);
+        launch_beam_eval(b, s);
+      } else {
+        launch_beam_table(b, s);
+      }
+    });
     v.f0 = f0;
     v.nf = nf;
     int bad = 0;
     timed(c, GTOD_KERNEL_SRC_CONV, 2.0 * (double)nn * nn * nf, s,
-          [&] { bad = launch_source_conv(v, s); });
+          [&] { bad = fft ? launch_source_fft(v, s) : launch_source_conv(v, s); });
     if (bad) return fail(c, GTOD_EDEVICE, "source convolution needs more LDS than the device allows");
   }
   HIP_TRY(c, hipGetLastError());

@@ -1270,6 +1270,18 @@ gtod_status gtod_reduce(gtod_ctx* c, const gtod_reduce_desc* d, void* hip_stream
   int64_t kg = avail > 0 ? K : 0;
   if (maps) kg = avail > 0 ? std::min<int64_t>(K, (avail - 256) / per_ch) : 0;
   if (kg < 1) return fail(c, GTOD_EINVAL, "workspace too small for one channel of the reduction");
+  // scratch of the faster kernels, where there is room for it as well
+  const int64_t tiles = (T + kRdTile - 1) / kRdTile;
+  const int64_t poly = round_up(K * kRdPoly * 8, 256);
+  const int64_t range = round_up((2 + 2 * ((T + 255) / 256)) * 8, 256);
+  const int64_t runs = maps ? (int64_t)P * tiles * kRdTile * 6 + round_up((int64_t)P * tiles * 4, 256) : 0;
+  const int64_t extra = poly + range + runs;
+  bool fast = avail > extra;
+  if (fast && maps) {
+    const int64_t n = (avail - extra - 256) / per_ch;
+    fast = n >= 1;
+    if (fast) kg = std::min<int64_t>(K, n);
+  }
 
   const int slot = w->slot;
   w->slot = (w->slot + 1) % kSlots;
@@ -1309,7 +1321,8 @@ gtod_status gtod_reduce(gtod_ctx* c, const gtod_reduce_desc* d, void* hip_stream
   a.pwv_ld = d->pwv_ld;
   a.pwv_len = d->pwv_len;
   a.pwv_host = d->pwv_mean_mm;
-  a.scan_tab = (double2*)ws;
+  a.scan_phi = (double*)ws;
+  a.scan_th = a.scan_phi + T;
   a.lnz = (double*)(ws + round_up(T * 16, 256));
   a.pwv_mean = (double*)(ws + round_up(T * 16, 256) + round_up(K * 8, 256));
   a.tod = d->tod;
@@ -1320,6 +1333,16 @@ gtod_status gtod_reduce(gtod_ctx* c, const gtod_reduce_desc* d, void* hip_stream
   a.map = d->map;
   a.weight = d->weight;
   char* grp = ws + fixed;
+  if (fast) {
+    a.poly = (double*)grp;
+    a.range = (double*)(grp + poly);
+    if (maps) {
+      a.runs = (uint32_t*)(grp + poly + range);
+      a.perm = (uint16_t*)(a.runs + (int64_t)P * tiles * kRdTile);
+      a.n_runs = (int*)(a.perm + (int64_t)P * tiles * kRdTile);
+    }
+    grp += extra;
+  }
   a.M = maps ? (double*)grp : nullptr;
   a.stats = maps ? (double2*)(grp + round_up(kg * T * 8, 256)) : nullptr;
   launch_reduce_setup(a, s);

@@ -135,6 +135,23 @@ __device__ __forceinline__ void dft_inv(float2 (&v)[1 << LGR]) {
   for (int r = 0; r < R; ++r) v[r] = u[r];
 }
 
+// v[r] times w^r for w = e^{2 pi i k 2^sh / 4096}: w^1, w^2, w^4, w^8 from the
+// table, the other powers as products of at most four of them.
+template <int LGR>
+__device__ __forceinline__ void twiddle_powers(float2 (&v)[1 << LGR], const float2* __restrict__ tab,
+                                               int k, int sh) {
+  constexpr int R = 1 << LGR;
+  float2 wp[R];
+  wp[0] = make_float2(1.f, 0.f);
+#pragma unroll
+  for (int b = 0; b < LGR; ++b) wp[1 << b] = tab[(k << b) << sh];
+#pragma unroll
+  for (int r = 3; r < R; ++r)
+    if (r & (r - 1)) wp[r] = cmul(wp[r & (r - 1)], wp[r & -r]);
+#pragma unroll
+  for (int r = 1; r < R; ++r) v[r] = cmul(v[r], wp[r]);
+}
+
 // Element i of transform t: pass 1 keeps transforms contiguous with one
 // float2 of padding after every 16; pass 2 interleaves them.
 struct AddrPadded {
@@ -171,19 +188,7 @@ __device__ __forceinline__ void stockham_pass(float2* buf, Addr addr, int lgL, i
 #pragma unroll
       for (int r = 0; r < R; ++r) v[gi][r] = buf[addr(t, j + (r << lgJ))];
       if (lgNs > 0) {
-        // w^r for w = e^{2 pi i k / (S R)}: w^1, w^2, w^4, w^8 from the
-        // table, the other powers as products of at most four of them
-        const int k = j & ((1 << lgNs) - 1);
-        const int sh = 12 - lgNs - LGR;
-        float2 wp[R];
-        wp[0] = make_float2(1.f, 0.f);
-#pragma unroll
-        for (int b = 0; b < LGR; ++b) wp[1 << b] = tab[(k << b) << sh];
-#pragma unroll
-        for (int r = 3; r < R; ++r)
-          if (r & (r - 1)) wp[r] = cmul(wp[r & (r - 1)], wp[r & -r]);
-#pragma unroll
-        for (int r = 1; r < R; ++r) v[gi][r] = cmul(v[gi][r], wp[r]);
+        twiddle_powers<LGR>(v[gi], tab, j & ((1 << lgNs) - 1), 12 - lgNs - LGR);
       }
       dft_inv<LGR>(v[gi]);
     }
@@ -250,7 +255,6 @@ __device__ __forceinline__ void store_out(const PinkArgs& a, int64_t series,
   }
 }
 
-
 }  // namespace
 
 // Twiddle table: entry m holds e^{2 pi i m / 4096}.
@@ -264,9 +268,10 @@ __global__ void k_pink_tables(float2* tab) {
 // once; every Z_k is built from X_k and X_{M-k} held in LDS, two at a time
 // (e^{2 pi i (M-k)/N} = -conj e^{2 pi i k/N}).
 // Dynamic LDS: one or two padded transforms of M2 values; EMAX bounds the
-// values per workgroup.  LGM2 > 0 fixes lg M2 at compile time (the length
-// every two-pass series uses), so that the transform's index arithmetic
-// folds into constants; LGM2 = 0 takes it from the arguments.
+// values per workgroup.  LGM2 > 0 fixes lg M2 at compile time, so that the
+// transform's index arithmetic folds into constants; LGM2 = 0 takes it from
+// the arguments.  For series of one pass (M <= 2048), and of columns longer
+// than 2048 (the others: k_pink_pairs).
 template <int EMAX, int LGM2>
 __global__ __launch_bounds__(256) void k_pink_pass1(PinkArgs a) {
   extern __shared__ float2 buf[];
@@ -367,32 +372,220 @@ __global__ __launch_bounds__(256) void k_pink_pass1(PinkArgs a) {
   }
 }
 
-// Pass 2 for at most EMAX = 2^(lgM1 + lgB2) elements per workgroup, held
-// in dynamic LDS of exactly that size (small blocks keep many workgroups
-// per CU, which is what this memory-bound pass needs).
-// LGM1 > 0 fixes lg M1 at compile time for series whose columns are
-// 2048 long (lg M2 = 11), so that the index arithmetic folds; LGM1 = 0
-// takes the lengths from the arguments.
-template <int EMAX, int LGM1>
+// Pass 1 at lg M2 = 11 and M1 >= 2: a workgroup takes the columns k1 and M1 -
+// k1, or 0 and M1 / 2.  A thread draws X_k and X_{M-k} of its 8 pairs and writes their Z to LDS; two passes of radix 16 in
+// LDS (thread (t, j) = one group of transform t), then one of radix 8 whose
+// outputs, tid + 256 s of both transforms, are stored from registers.  Every
+// LDS address is one of three per-thread bases plus a constant, and every
+// twiddle but each sequence's first is a constant or uniform:
+//   e^{2 pi i k / N}, k = k1 + M1 (tid + 256 i):       first times e^{2 pi i i / 16}
+//   e^{2 pi i k1 m2 / M}, m2 = tid + 256 s:            first times e^{2 pi i k1 s / (8 M1)}
+// Bound by the vector ALU (39 of its instructions per bin are Philox).  2429
+// series of 2^20 samples: 3.81 ms; 6.03 with run-time strides, five sincospi per
+// sequence and the bins taken through LDS.
+__global__ __launch_bounds__(256) void k_pink_pairs(PinkArgs a) {
+  constexpr int kM2 = 1 << kPinkLgM2, kCol = kM2 + (kM2 >> 4), kStep = 256 + 16;
+  __shared__ float2 buf[2 * kCol];
+  const int tid = threadIdx.x, lane = tid & 63, sl = blockIdx.y;
+  const int64_t series = a.s0 + sl;
+  const int p = (int)(series / a.K);
+  const int k = (int)(series % a.K);
+  const float sc = a.scale[k];
+  const float halpha = -0.5f * a.alpha[k];
+  const float fstep = (float)(a.fs / (double)a.N);
+  const int M1 = a.M1, lgM = a.lgM1 + kPinkLgM2;
+  const uint32_t M = (uint32_t)a.M, step = (uint32_t)M1 * 256u;
+  const int col[2] = {(int)blockIdx.x, blockIdx.x ? M1 - (int)blockIdx.x : M1 / 2};
+  auto draw = [&](uint32_t j) {
+    const u32x4 o = philox10(u32x4{j, (uint32_t)k, (uint32_t)(a.pix0 + p), 1u}, a.key0, a.key1);
+    float zc, zs;
+    box_muller(o.x, o.y, &zc, &zs);
+    // power law from the hardware log2 and exp2 (about one ulp each)
+    const float cj = sc * __builtin_amdgcn_exp2f(halpha * __builtin_amdgcn_logf((float)j * fstep));
+    return make_float2(cj * zc, cj * zs);
+  };
+  // Z_k = (X_k + conj X_{M-k}) + i w (X_k - conj X_{M-k}); Z_{M-k} is
+  // conj E - i conj(w O)
+  auto pair = [&](uint32_t j, float2 w, float2* zk, float2* zm) {
+    const float2 xa = draw(j), xb = draw(M - j);
+    const float2 ev = make_float2(xa.x + xb.x, xa.y - xb.y);
+    const float2 wo = cmul(w, make_float2(xa.x - xb.x, xa.y + xb.y));
+    *zk = make_float2(ev.x - wo.y, ev.y + wo.x);
+    *zm = make_float2(ev.x + wo.y, wo.x - ev.y);
+  };
+  float2* const up = buf + tid + (tid >> 4);
+  float2* const down = buf + (255 - tid) + ((255 - tid) >> 4);
+  if (blockIdx.x) {
+    const uint32_t j0 = (uint32_t)col[0] + (uint32_t)M1 * tid;
+    const float2 w0 = twiddle(j0, lgM + 1);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      pair(j0 + step * i, mul_w16(w0, i), up + kStep * i, down + kCol + kStep * (7 - i));
+  } else {
+    // columns 0 (rows u and 2048 - u) and M1 / 2 (u and 2047 - u), each its
+    // own mirror; Z_0 = 0, Z_{M/2} = 2 conj X_{M/2}
+    float2* const down0 = buf + (256 - tid) + ((256 - tid) >> 4);
+    const uint32_t j0 = (uint32_t)M1 * tid, j1 = j0 + (uint32_t)col[1];
+    const float2 w0 = twiddle(j0, lgM + 1), w1 = twiddle(j1, lgM + 1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      pair(j1 + step * i, mul_w16(w1, i), up + kCol + kStep * i, down + kCol + kStep * (7 - i));
+      if (i || tid) {
+        pair(j0 + step * i, mul_w16(w0, i), up + kStep * i, down0 + kStep * (7 - i));
+      } else {
+        const float2 x = draw(M / 2);
+        buf[0] = make_float2(0.f, 0.f);
+        buf[4 * kStep] = make_float2(2.f * x.x, -2.f * x.y);
+      }
+    }
+  }
+  __syncthreads();
+  {
+    const int t = tid >> 7, j = tid & 127;
+    float2* const in = buf + t * kCol + j + (j >> 4);
+    float2 v[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] = in[(128 + 8) * r];
+    dft_inv<4>(v);
+    __syncthreads();
+    float2* const out = buf + t * kCol + 17 * j;
+#pragma unroll
+    for (int s = 0; s < 16; ++s) out[s] = v[s];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] = in[(128 + 8) * r];
+    twiddle_powers<4>(v, a.tab, j & 15, 4);
+    dft_inv<4>(v);
+    __syncthreads();
+    float2* const out2 = buf + t * kCol + (j >> 4) * kStep + (j & 15);
+#pragma unroll
+    for (int s = 0; s < 16; ++s) out2[17 * s] = v[s];
+  }
+  __syncthreads();
+  // lanes 0 - 15: the uniform factors of the two columns
+  const float2 f = twiddle((uint32_t)((lane & 8 ? col[1] : col[0]) * (lane & 7)) &
+                               (uint32_t)(8 * M1 - 1),
+                           a.lgM1 + 3);
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const float2* const in = buf + c * kCol + tid + (tid >> 4);
+    float2 v[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) v[r] = in[kStep * r];
+    twiddle_powers<3>(v, a.tab, tid, 1);
+    dft_inv<3>(v);
+    const float2 w0 = twiddle((uint32_t)((uint64_t)col[c] * tid) & (uint32_t)(a.M - 1), lgM);
+    float2* const dst = a.scratch + (((int64_t)sl * M1 + col[c]) << kPinkLgM2) + tid;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      float2 w = w0;
+      if (s) {
+        const float2 u = make_float2(
+            __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, f.x), 8 * c + s)),
+            __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, f.y), 8 * c + s)));
+        w = cmul(w, u);
+      }
+      dst[256 * s] = cmul(v[s], w);
+    }
+  }
+}
+
+// Pass 2 for columns of 2048 (lg M2 = 11) and LGM1 <= 8: bound by memory, so
+// each thread has its 16 (or M1, if fewer) elements in flight at once, straight
+// into the registers of the first radix, and the last radix stores from
+// registers; what lies between goes through LDS once, or not at all up to M1 =
+// 16.  Columns fastest across lanes, so that every access runs over at least
+// 128 B.  2429 series of 2^20 samples (576000 kept): 3.22 ms, 4.66 with both
+// sides staged in LDS; 13680 series of 2^14: 0.35 ms, 1.01.
+template <int LGM1>
+__global__ __launch_bounds__(256) void k_pink_columns(PinkArgs a) {
+  constexpr int LG1 = LGM1 < 4 ? LGM1 : 4, LG2 = LGM1 - LG1, R1 = 1 << LG1;
+  constexpr int kLgB = 8 - LG2, B = 1 << kLgB;     // columns per workgroup
+  const int tid = threadIdx.x, t = tid & (B - 1), j = tid >> kLgB;
+  const int64_t m20 = (int64_t)blockIdx.x * B;
+  const int64_t series = a.s0 + blockIdx.y;
+  const float2* const src = a.scratch + ((int64_t)blockIdx.y << (LGM1 + kPinkLgM2)) + m20 + t +
+                            ((int64_t)j << kPinkLgM2);
+  float* const dst = a.tod + series * a.out_ld;
+  const bool pairs = ((a.out_ld & 1) == 0) && ((reinterpret_cast<uintptr_t>(a.tod) & 7) == 0);
+  // element e of v is output m1(e) of column m20 + col(e)
+  auto store = [&](const auto& v, auto m1, auto col, int n) {
+    if (!pairs) {
+#pragma unroll
+      for (int e = 0; e < n; ++e)
+        store_out(a, series, ((int64_t)m1(e) << kPinkLgM2) + m20 + col(e), v[e]);
+      return;
+    }
+    float2 old[R1];
+    if (a.accumulate) {
+#pragma unroll
+      for (int e = 0; e < n; ++e) {
+        const int64_t x = 2 * (((int64_t)m1(e) << kPinkLgM2) + m20 + col(e));
+        old[e] = x + 1 < a.t_total ? *reinterpret_cast<const float2*>(dst + x) : make_float2(0.f, 0.f);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < n; ++e) {
+      const int64_t x = 2 * (((int64_t)m1(e) << kPinkLgM2) + m20 + col(e));
+      if (x + 1 < a.t_total) {
+        float2 z = v[e];
+        if (a.accumulate) z = cadd(old[e], z);
+        *reinterpret_cast<float2*>(dst + x) = z;
+      } else if (x < a.t_total) {      // the last sample of an odd length
+        if (a.accumulate) dst[x] += v[e].x;
+        else dst[x] = v[e].x;
+      }
+    }
+  };
+  float2 v[R1];
+#pragma unroll
+  for (int r = 0; r < R1; ++r)      // read once, past the caches
+    v[r] = __builtin_bit_cast(float2, __builtin_nontemporal_load(reinterpret_cast<const double*>(
+                                          src + ((int64_t)r << (LG2 + kPinkLgM2)))));
+  dft_inv<LG1>(v);
+  if constexpr (LG2 == 0) {
+    store(v, [](int e) { return e; }, [&](int) { return t; }, R1);
+  } else {
+    __shared__ float2 buf[1 << 12];
+#pragma unroll
+    for (int s = 0; s < R1; ++s) buf[(((j << 4) + s) << kLgB) + t] = v[s];
+    __syncthreads();
+    constexpr int R2 = 1 << LG2, G = 16 / R2;      // transforms of length R2 per thread
+    float2 o[16];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const int q = tid + 256 * g, c = q & (B - 1), k = q >> kLgB;
+      float2 u[R2];
+#pragma unroll
+      for (int r = 0; r < R2; ++r) u[r] = buf[((k + 16 * r) << kLgB) + c];
+      twiddle_powers<LG2>(u, a.tab, k, 8 - LG2);
+      dft_inv<LG2>(u);
+#pragma unroll
+      for (int s = 0; s < R2; ++s) o[g * R2 + s] = u[s];
+    }
+    store(o, [&](int e) { return ((tid + 256 * (e / R2)) >> kLgB) + 16 * (e % R2); },
+          [&](int e) { return (tid + 256 * (e / R2)) & (B - 1); }, 16);
+  }
+}
+
+// Pass 2 for other lengths: 2^(lgM1 + lgB2) elements per workgroup, held in
+// dynamic LDS of exactly that size.
 __global__ __launch_bounds__(256) void k_pink_pass2(PinkArgs a) {
   extern __shared__ float2 buf[];
   const int nb = blockIdx.x;
   const int sl = blockIdx.y;
   const int64_t series = a.s0 + sl;
-  constexpr int kLgB2 = LGM1 > 0 ? (12 - LGM1 < kPinkLgB2 ? 12 - LGM1 : kPinkLgB2) : 0;
-  const int lgM1 = LGM1 > 0 ? LGM1 : a.lgM1;
-  const int lgM2 = LGM1 > 0 ? kPinkLgM2 : a.lgM2;
-  const int M2 = 1 << lgM2, lgB2 = LGM1 > 0 ? kLgB2 : a.lgB2, B2 = 1 << lgB2;
+  const int M2 = 1 << a.lgM2, lgB2 = a.lgB2, B2 = 1 << lgB2;
   const int m20 = nb << lgB2;
-  const float2* src = a.scratch + ((int64_t)sl << (lgM1 + lgM2));
-  const int n = 1 << (lgM1 + lgB2);
+  const float2* src = a.scratch + ((int64_t)sl << (a.lgM1 + a.lgM2));
+  const int n = 1 << (a.lgM1 + lgB2);
   // element k1 of transform bb at k1 B2 + bb: both sides consecutive
   for (int idx = threadIdx.x; idx < n; idx += blockDim.x) {
     const int k1 = idx >> lgB2, bb = idx & (B2 - 1);
     buf[idx] = src[(int64_t)k1 * M2 + m20 + bb];
   }
   __syncthreads();
-  fft_inv<EMAX, true>(buf, AddrInterleaved{lgB2}, lgM1, lgB2, a.tab);
+  fft_inv<kLdsC, true>(buf, AddrInterleaved{lgB2}, a.lgM1, lgB2, a.tab);
   for (int idx = threadIdx.x; idx < n; idx += blockDim.x) {
     const int m1 = idx >> lgB2, bb = idx & (B2 - 1);
     store_out(a, series, (int64_t)m1 * M2 + m20 + bb, buf[idx]);
@@ -404,6 +597,10 @@ void launch_pink_tables(const PinkArgs& a, hipStream_t s) {
 }
 
 void launch_pink_pass1(const PinkArgs& a, hipStream_t s) {
+  if (a.lgM2 == kPinkLgM2 && a.M1 >= 2) {
+    hipLaunchKernelGGL(k_pink_pairs, dim3(a.M1 / 2, a.n_series), dim3(256), 0, s, a);
+    return;
+  }
   const int groups = a.M1 == 1 ? 1 : a.M1 / 2 + 1;
   const int e = (a.M1 == 1 ? 1 : 2) << a.lgM2;   // values per workgroup
   const size_t lds = (size_t)(e + (e >> 4)) * sizeof(float2);
@@ -417,26 +614,25 @@ void launch_pink_pass1(const PinkArgs& a, hipStream_t s) {
 }
 
 void launch_pink_pass2(const PinkArgs& a, hipStream_t s) {
-  const dim3 grid(a.M2 >> a.lgB2, a.n_series);
-  const int e = 1 << (a.lgM1 + a.lgB2);
-  const size_t lds = (size_t)e * sizeof(float2);
-#define GTOD_PASS2(EM, L) hipLaunchKernelGGL((k_pink_pass2<EM, L>), grid, dim3(256), lds, s, a)
-  if (a.lgM2 == kPinkLgM2 && a.lgB2 == std::min(kPinkLgB2, 12 - a.lgM1)) {
-    switch (a.lgM1) {   // e = 2^(lgM1 + lgB2) <= 4096
-      case 1: GTOD_PASS2(kLdsC / 2, 1); return;
-      case 2: GTOD_PASS2(kLdsC / 2, 2); return;
-      case 3: GTOD_PASS2(kLdsC / 2, 3); return;
-      case 4: GTOD_PASS2(kLdsC / 2, 4); return;
-      case 5: GTOD_PASS2(kLdsC / 2, 5); return;
-      case 6: GTOD_PASS2(kLdsC / 2, 6); return;
-      case 7: GTOD_PASS2(kLdsC / 2, 7); return;
-      case 8: GTOD_PASS2(kLdsC, 8); return;
-      default: break;
+  if (a.lgM2 == kPinkLgM2 && a.lgM1 <= 8) {
+    const int lg_cols = a.lgM1 <= 4 ? 8 : 12 - a.lgM1;
+    const dim3 grid(a.M2 >> lg_cols, a.n_series);
+#define GTOD_COLUMNS(L) \
+  case L: hipLaunchKernelGGL(k_pink_columns<L>, grid, dim3(256), 0, s, a); return
+    switch (a.lgM1) {
+      GTOD_COLUMNS(1);
+      GTOD_COLUMNS(2);
+      GTOD_COLUMNS(3);
+      GTOD_COLUMNS(4);
+      GTOD_COLUMNS(5);
+      GTOD_COLUMNS(6);
+      GTOD_COLUMNS(7);
+      GTOD_COLUMNS(8);
     }
+#undef GTOD_COLUMNS
   }
-  if (e <= kLdsC / 2) GTOD_PASS2(kLdsC / 2, 0);
-  else GTOD_PASS2(kLdsC, 0);
-#undef GTOD_PASS2
+  const size_t lds = sizeof(float2) << (a.lgM1 + a.lgB2);
+  hipLaunchKernelGGL(k_pink_pass2, dim3(a.M2 >> a.lgB2, a.n_series), dim3(256), lds, s, a);
 }
 
 __global__ void k_philox(const uint32_t* ctr, uint32_t* out, int64_t n,

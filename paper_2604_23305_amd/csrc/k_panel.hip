@@ -410,9 +410,13 @@ void launch_panel(const PanelArgs& a0, hipStream_t s) {
   PanelArgs a = a0;
   const int64_t rows = (int64_t)a.n_pix * a.Tpad;
   const int passes = (a.Fp + kTileBins - 1) / kTileBins;
-  // few rows: fewer of them per workgroup, and a workgroup per bin pass
-  a.rows_wg = rows >= 1024 * kPanelRows ? kPanelRows : 8;
-  const dim3 grid((unsigned)(rows / a.rows_wg), rows >= 1024 * kPanelRows ? 1 : passes);
+  // A workgroup per bin pass and fewer rows in each as long as that spreads the
+  // rows more evenly over the card (us at 1750 bins, against 32 rows and all
+  // passes in one: 33621 rows 90 / 106, 42000 109 / 119, 56000 135 / 146, 84000
+  // 200 / 206); in longer launches a row's record serves all its passes (526848
+  // rows of 3000 bins: 1.59 ms, 1.64 with one pass each).
+  a.rows_wg = rows < 1024 * kPanelRows ? 8 : (rows < 2048 * kPanelRows ? 16 : kPanelRows);
+  const dim3 grid((unsigned)(rows / a.rows_wg), rows < 4096 * kPanelRows ? passes : 1);
   if (a.n_buckets <= 1) {
     hipLaunchKernelGGL(k_panel, grid, dim3(256), 0, s, a);
     return;

@@ -63,3 +63,26 @@ def test_sorted_rows_match_rows_in_order(F, pitch, offset):
     # far from the reference the bound is that of an FP32 sum of F terms
     e = rel_err(x.p_kid.cpu().numpy(), ref["p_kid"])
     assert e.max() <= max(1e-6, (F + 8) * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("T", [4680, 4700, 9340, 9380, 18720])
+def test_every_spread_of_the_rows_gives_the_same_outputs(T):
+    """7 pixels on either side of 32768, 65536 and 131072 panel rows, two
+    passes of bins, in one window and in windows of 1792 samples."""
+    sc = tiny_scenario(F=1030, K=2, P=7, T=T, filt="matrix")
+    got = []
+    for step in (T, 1792):
+        ctx = new_ctx()
+        try:
+            run = g.ScenarioRun(ctx, sc)
+            out = run.alloc(with_p_kid=True, with_sigma=True, with_pwv=True)
+            g.simulate_tod(ctx, [run.signal_job(out, a, min(a + step, T))
+                                 for a in range(0, T, step)])
+            torch.cuda.synchronize()
+            got.append((out, g.counters(ctx)))
+        finally:
+            g.free(ctx)
+    (x, cx), (y, cy) = got
+    for name in ("tod", "p_kid", "sigma", "pwv"):
+        assert torch.equal(getattr(x, name), getattr(y, name)), name
+    assert cx == cy

@@ -210,9 +210,10 @@ struct ReduceArgs {
   double* lnz;                // scratch [K] ln of the channel zenith transmission
   double* scan_phi;           // scratch [T]
   double* scan_th;            // scratch [T]
-  double* range;              // scratch [2 + 2 ceil(T / 256)]: elevation offsets'
-                              // middle, 1 / half width; (min, max) of 256 samples
-  double* poly;               // scratch [K][kRdPoly], or null: no polynomials
+  // scratch [P][T], or null: cosecants of the elevation, as the common-mode and
+  // as the gridding kernel adds the angles
+  double* csc_common;
+  double* csc_grid;
   uint32_t* runs;             // scratch [P][tiles][kRdTile], or null
   uint16_t* perm;             // scratch [P][tiles][kRdTile]
   int* n_runs;                // scratch [P][tiles]
@@ -302,8 +303,6 @@ hipStream_t ctx_sink_stream(gtod_ctx* c, int which);
 // A tile's samples, sorted by cell, in runs of at most kRdRun: start (11 bits),
 // length - 1 (5), cell (12), cell in several runs (1).
 constexpr int kRdTile = 2048, kRdRun = 8;
-constexpr int kRdTerms = 7;                      // of a polynomial
-constexpr int kRdPoly = 2 * kRdTerms + 1;        // 1 / eta - 1, 1 / (1 - eta), 1 if unusable
 void launch_reduce_setup(const ReduceArgs& a, hipStream_t s);
 void launch_reduce_common(const ReduceArgs& a, hipStream_t s);
 int launch_reduce_grid(const ReduceArgs& a, hipStream_t s);  // 0 ok

@@ -16,27 +16,24 @@
 // without maps, T*), grid (T* and cell sums), combine (one thread per
 // (channel, cell)).  The common and grid kernels each stream the TOD once.
 //
-// r = 1 / eta - 1 and u = 1 / (1 - eta) of a channel depend on the elevation
-// alone, and a scan covers little of it: both are polynomials of degree 6 over
-// the call's elevations, from Chebyshev nodes where they are evaluated with
-// expm1.  T* = T_b + r (T_b - M), M = mean of u T_b: seven multiply-adds per
-// sample in place of an expm1 and a division.  A channel whose degree-6 term is
-// not below 2^-49 of the value (wide scans, opaque channels) is evaluated
-// sample by sample.
+// The cosecants are tabulated once per call for all channels; each sample then
+// takes one FP64 expm1 (eta = 1 + expm1(ln eta), so 1 - eta keeps its relative
+// precision) and a division in either kernel, which is what bounds them.
+// (Polynomials in elevation in their place take 2.9 ms in all, but the last bits
+// of T* decide the weight of a cell whose few samples nearly coincide.)
 //
 // Cell sums: the samples of a tile of time, sorted once per spaxel by cell, are
 // summed by one thread per run of a cell and added to the block's sums in LDS,
 // without atomics except for cells of more than one run.
 //
-// 49 spaxels x 347 channels x 57600 samples, T* and 31 x 31 maps: 2.88 ms (8.37
-// with an expm1 and a division per sample and two LDS atomics, which run at a
-// lane per clock).  Common 0.59 ms (6.6 TB/s of TOD; 2.2 before), grid 2.16
-// (6.1): 3.9 GB read, 4 GB written, and between barriers neither they nor the
-// multiply-adds (0.9 ms) nor LDS (0.7 ms) are hidden entirely.  The sort, 70 us,
-// serves all channels.
+// 49 spaxels x 347 channels x 57600 samples, T* and 31 x 31 maps: 4.15 ms (8.37
+// with a sine and a division per spaxel, sample and four channels and two LDS
+// atomics per sample, which run at a lane per clock).  Common 1.03 ms (2.2
+// before), grid 2.97 (6.1): about 60 FP64 instructions a sample, 1.5 ms of the
+// grid's time, beside 3.9 GB read and 4 GB written.  The sort, 70 us, serves all
+// channels.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <cmath>
 
 #include "gtod_internal.h"
@@ -60,51 +57,6 @@ __device__ double block_sum_256(double v, double* s) {
   return r;
 }
 
-// Least and largest over the block of values that are not NaN.
-__device__ inline void block_range(double* lo, double* hi) {
-  __shared__ double s[2][kRdThreads / 64];
-#pragma unroll
-  for (int st = 32; st > 0; st >>= 1) {
-    *lo = fmin(*lo, __shfl_xor(*lo, st));
-    *hi = fmax(*hi, __shfl_xor(*hi, st));
-  }
-  if ((threadIdx.x & 63) == 0) {
-    s[0][threadIdx.x >> 6] = *lo;
-    s[1][threadIdx.x >> 6] = *hi;
-  }
-  __syncthreads();
-  *lo = fmin(fmin(s[0][0], s[0][1]), fmin(s[0][2], s[0][3]));
-  *hi = fmax(fmax(s[1][0], s[1][1]), fmax(s[1][2], s[1][3]));
-  __syncthreads();
-}
-
-// Monomial coefficients from the values at the Chebyshev nodes; false if the
-// last term is not negligible.
-__device__ inline bool fit(const double* f, double* m) {
-  constexpr int N = kRdTerms;
-  double least = INFINITY, c[N], t0[N], t1[N];
-  for (int i = 0; i < N; ++i) least = fmin(least, fabs(f[i]));
-  for (int n = 0; n < N; ++n) {
-    double s = 0.0;
-    for (int i = 0; i < N; ++i) s += f[i] * cospi(n * (i + 0.5) / N);
-    c[n] = s * (n ? 2.0 : 1.0) / N;
-    t0[n] = n == 0;
-    t1[n] = n == 1;
-    m[n] = 0.0;
-  }
-  for (int n = 0; n < N; ++n) {
-    for (int i = 0; i < N; ++i) m[i] += c[n] * t0[i];
-    double below = 0.0;
-    for (int i = 0; i < N; ++i) {
-      const double t2 = 2.0 * below - t0[i];
-      below = t1[i];
-      t0[i] = t1[i];
-      t1[i] = t2;
-    }
-  }
-  return fabs(c[N - 1]) <= 0x1p-49 * least && least > 0.0 && least < INFINITY;
-}
-
 __device__ inline int map_cell(const ReduceArgs& a, double x, double y) {
   const double gx = floor((x + a.half) / a.dcell + 0.5);
   const double gy = floor((y + a.half) / a.dcell + 0.5);
@@ -117,20 +69,22 @@ __device__ inline int map_cell(const ReduceArgs& a, double x, double y) {
 
 __global__ __launch_bounds__(kRdThreads) void k_rd_scan(ReduceArgs a) {
   const int64_t t = (int64_t)blockIdx.x * kRdThreads + threadIdx.x;
-  double phi = NAN, th = NAN;
-  if (t < a.T) {
-    scan_offsets(a.scan_kind, a.r_petal, a.omega, a.Omega, a.traj, a.t0 + t,
-                 a.f_s, &phi, &th);
-    a.scan_phi[t] = phi;
-    a.scan_th[t] = th;
-  }
-  if (!a.poly) return;
-  double lo = th, hi = th;
-  block_range(&lo, &hi);
-  if (threadIdx.x == 0) {
-    a.range[2 + 2 * blockIdx.x] = lo;
-    a.range[3 + 2 * blockIdx.x] = hi;
-  }
+  if (t >= a.T) return;
+  double phi, th;
+  scan_offsets(a.scan_kind, a.r_petal, a.omega, a.Omega, a.traj, a.t0 + t,
+               a.f_s, &phi, &th);
+  a.scan_phi[t] = phi;
+  a.scan_th[t] = th;
+}
+
+// Cosecants of spaxel blockIdx.y.
+__global__ __launch_bounds__(kRdThreads) void k_rd_csc(ReduceArgs a) {
+  const int64_t t = (int64_t)blockIdx.x * kRdThreads + threadIdx.x;
+  if (t >= a.T) return;
+  const int p = blockIdx.y;
+  const double th = a.scan_th[t];
+  a.csc_common[p * a.T + t] = 1.0 / sin((th + a.theta0) + a.dtheta[p]);
+  if (a.csc_grid) a.csc_grid[p * a.T + t] = 1.0 / sin(th + (a.theta0 + a.dtheta[p]));
 }
 
 // Mean zenith PWV (one block, fixed-order sums), then ln eta_z,k (one
@@ -168,53 +122,7 @@ __global__ __launch_bounds__(kRdThreads) void k_rd_channel(ReduceArgs a) {
   }
   const double N = block_sum_256(num, s);
   const double D = block_sum_256(den, s);
-  const double lz = (D > 0.0) ? log(N / D) : NAN;
-  if (threadIdx.x == 0) a.lnz[k] = lz;
-  if (!a.poly) return;
-  // elevation offsets of the call
-  double lo = NAN, hi = NAN, plo = NAN, phi = NAN;
-  for (int64_t i = threadIdx.x; i < (a.T + kRdThreads - 1) / kRdThreads; i += kRdThreads) {
-    lo = fmin(lo, a.range[2 + 2 * i]);
-    hi = fmax(hi, a.range[3 + 2 * i]);
-  }
-  for (int p = threadIdx.x; p < a.P; p += kRdThreads) {
-    plo = fmin(plo, a.dtheta[p]);
-    phi = fmax(phi, a.dtheta[p]);
-  }
-  block_range(&lo, &hi);
-  block_range(&plo, &phi);
-  const double mid = 0.5 * ((lo + plo) + (hi + phi)), half = 0.5 * ((hi + phi) - (lo + plo));
-  if (k == 0 && threadIdx.x == 0) {
-    a.range[0] = mid;
-    a.range[1] = half > 0.0 ? 1.0 / half : 0.0;
-  }
-  double* const r = s;
-  double* const u = s + kRdTerms;
-  if (threadIdx.x < kRdTerms) {
-    const double x = cospi((threadIdx.x + 0.5) / kRdTerms);
-    const double y = lz / sin(a.theta0 + fma(half, x, mid));
-    r[threadIdx.x] = expm1(-y);
-    u[threadIdx.x] = -1.0 / expm1(y);
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double* const m = a.poly + (int64_t)k * kRdPoly;
-    bool ok = fit(r, m);
-    ok &= fit(u, m + kRdTerms);
-    // at 1 / eta above 2^30 a sample's own eta - 1 no longer holds eta to FP32
-    for (int i = 0; i < kRdTerms; ++i) ok &= r[i] > 0.0 && r[i] < 0x1p30;
-    m[2 * kRdTerms] = ok ? 0.0 : 1.0;
-  }
-}
-
-// Polynomials of a channel, wave-uniform, through the scalar cache.
-typedef const __attribute__((address_space(4))) double* RdConst;
-
-__device__ inline double poly_at(const double* c, double x) {
-  double v = c[kRdTerms - 1];
-#pragma unroll
-  for (int n = kRdTerms - 2; n >= 0; --n) v = fma(v, x, c[n]);
-  return v;
+  if (threadIdx.x == 0) a.lnz[k] = (D > 0.0) ? log(N / D) : NAN;
 }
 
 // Four samples of a row; n < 4 at its end.  Rows start at any multiple of 4 B,
@@ -250,115 +158,56 @@ __device__ inline void store4(T* p, int n, const T* v) {
   }
 }
 
-// One thread per 4 samples and kRdChan channels of the group: enough loads in
-// flight per spaxel, and the channels' polynomials stay in scalar registers.
-constexpr int kRdChan = 4;
+// One thread per sample and kRdChan channels of the group.
+constexpr int kRdChan = 8;
 __global__ __launch_bounds__(kRdThreads) void k_rd_common(ReduceArgs a) {
-  const int64_t t = ((int64_t)blockIdx.x * kRdThreads + threadIdx.x) * 4;
+  const int64_t t = (int64_t)blockIdx.x * kRdThreads + threadIdx.x;
   const int kl0 = blockIdx.y * kRdChan;
   if (t >= a.T) return;
-  const int nt = (int)min(a.T - t, (int64_t)4);
   const int nk = min(kRdChan, a.kg - kl0);
-  double lz[kRdChan], cu[kRdChan][kRdTerms];
-  bool single = !a.poly;
-  const RdConst poly = (RdConst)(uintptr_t)a.poly;
-  const RdConst range = (RdConst)(uintptr_t)a.range;
+  double lz[kRdChan], sum[kRdChan];
 #pragma unroll
   for (int q = 0; q < kRdChan; ++q) {
-    const int k = a.k0 + min(kl0 + q, a.kg - 1);     // dead slots repeat the last channel
-    lz[q] = ((RdConst)(uintptr_t)a.lnz)[k];
-    if (a.poly) {
-#pragma unroll
-      for (int n = 0; n < kRdTerms; ++n) cu[q][n] = poly[k * kRdPoly + kRdTerms + n];
-      single |= poly[k * kRdPoly + 2 * kRdTerms] != 0.0;
-    }
+    lz[q] = a.lnz[a.k0 + min(kl0 + q, a.kg - 1)];    // dead slots repeat the last channel
+    sum[q] = 0.0;
   }
-  double th[4], sum[kRdChan][4];
-  load4<Double4>(a.scan_th + t, nt, th);
-#pragma unroll
-  for (int q = 0; q < kRdChan; ++q)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sum[q][i] = 0.0;
+  const double th = a.scan_th[t] + a.theta0;
   const int64_t rowK = a.ld;                      // stride between channels
-  auto row = [&](int p, int q) {
-    return ((int64_t)p * a.K + a.k0 + min(kl0 + q, a.kg - 1)) * rowK + t;
+  auto cosecant = [&](int p) {
+    return a.csc_common ? a.csc_common[p * a.T + t] : 1.0 / sin(th + a.dtheta[p]);
   };
-  const double mid = single ? 0.0 : range[0], inv = single ? 0.0 : range[1];
-  if (!single) {
-#pragma unroll 2
-    for (int p = 0; p < a.P; ++p) {
-      if (!a.off[p]) continue;
-      const double xp = (a.dtheta[p] - mid) * inv;
-      float v[kRdChan][4];
+  auto load = [&](int p, float (&v)[kRdChan]) {
+    const float* src = a.tod + ((int64_t)p * a.K + a.k0 + kl0) * rowK + t;
 #pragma unroll
-      for (int q = 0; q < kRdChan; ++q) load4<Float4>(a.tod + row(p, q), nt, v[q]);
+    for (int q = 0; q < kRdChan; ++q) v[q] = src[min(q, nk - 1) * rowK];
+  };
+  float v[kRdChan], w[kRdChan];
+  load(0, v);
+  for (int p = 0; p < a.P; ++p) {
+    if (p + 1 < a.P) load(p + 1, w);
+    if (a.off[p]) {
+      const double csc = cosecant(p);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const double x = fma(th[i], inv, xp);
-#pragma unroll
-        for (int q = 0; q < kRdChan; ++q)
-          sum[q][i] = fma((double)v[q][i], poly_at(cu[q], x), sum[q][i]);
-      }
+      for (int q = 0; q < kRdChan; ++q) sum[q] += (double)v[q] / -expm1(lz[q] * csc);
     }
-  } else {
-    for (int p = 0; p < a.P; ++p) {
-      if (!a.off[p]) continue;
-      for (int i = 0; i < nt; ++i) {
-        const double csc = 1.0 / sin(a.scan_th[t + i] + a.theta0 + a.dtheta[p]);
 #pragma unroll
-        for (int q = 0; q < kRdChan; ++q) {
-          const double d = (double)a.tod[row(p, q) + i] / -expm1(lz[q] * csc);
-          // the samples' sums stay in registers: i is no compile-time index
-          sum[q][0] += i == 0 ? d : 0.0;
-          sum[q][1] += i == 1 ? d : 0.0;
-          sum[q][2] += i == 2 ? d : 0.0;
-          sum[q][3] += i == 3 ? d : 0.0;
-        }
-      }
-    }
+    for (int q = 0; q < kRdChan; ++q) v[q] = w[q];
   }
 #pragma unroll
-  for (int q = 0; q < kRdChan; ++q)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sum[q][i] /= (double)a.n_out;
-  if (a.M)
-#pragma unroll
-    for (int q = 0; q < kRdChan; ++q)
-      if (q < nk) store4<Double4, false>(a.M + (int64_t)(kl0 + q) * a.T + t, nt, sum[q]);
+  for (int q = 0; q < kRdChan; ++q) {
+    sum[q] /= (double)a.n_out;
+    if (q < nk && a.M) a.M[(int64_t)(kl0 + q) * a.T + t] = sum[q];
+  }
   if (!a.t_star || a.map_n > 0) return;
   for (int p = 0; p < a.P; ++p) {
-    float v[kRdChan][4];
-    if (!single) {
-      const double xp = (a.dtheta[p] - mid) * inv;
+    const double csc = cosecant(p);
+    load(p, v);
+    float* dst = a.t_star + ((int64_t)p * a.K + a.k0 + kl0) * rowK + t;
 #pragma unroll
-      for (int q = 0; q < kRdChan; ++q) load4<Float4>(a.tod + row(p, q), nt, v[q]);
-#pragma unroll
-      for (int q = 0; q < kRdChan; ++q) {
-        double cr[kRdTerms];
-        const int k = a.k0 + min(kl0 + q, a.kg - 1);
-#pragma unroll
-        for (int n = 0; n < kRdTerms; ++n) cr[n] = poly[k * kRdPoly + n];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const double d = v[q][i];
-          v[q][i] = (float)fma(poly_at(cr, fma(th[i], inv, xp)), d - sum[q][i], d);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const double csc = 1.0 / sin(th[i] + a.theta0 + a.dtheta[p]);
-#pragma unroll
-        for (int q = 0; q < kRdChan; ++q) {
-          const double em = expm1(lz[q] * csc);     // eta - 1
-          v[q][i] = i < nt ? (float)(((double)a.tod[row(p, q) + i] + em * sum[q][i]) / (1.0 + em))
-                           : 0.f;
-        }
-      }
+    for (int q = 0; q < kRdChan; ++q) {
+      const double em = expm1(lz[q] * csc);     // eta - 1
+      if (q < nk) dst[q * rowK] = (float)(((double)v[q] + em * sum[q]) / (1.0 + em));
     }
-#pragma unroll
-    for (int q = 0; q < kRdChan; ++q)
-      if (q < nk) store4<Float4, true>(a.t_star + row(p, q), nt, v[q]);
   }
 }
 
@@ -434,6 +283,13 @@ __global__ __launch_bounds__(kRdSortThreads) void k_rd_sort(ReduceArgs a) {
   if (tid == kRdSortThreads - 1) a.n_runs[tile] = at;
 }
 
+// The square rounded before it is added, as the atomics of k_rd_grid take it.
+__device__ inline double add_square(double s, double v) {
+  double q = v * v;
+  asm("" : "+v"(q));   // not fused into one multiply-add
+  return s + q;
+}
+
 // Barrier for LDS alone: loads of the next tile and stores stay in flight.
 __device__ inline void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -446,12 +302,10 @@ __device__ inline void lds_barrier() {
 // a run of a cell to a thread, added to the block's cell sums.  The variance is
 // (S2 - S1^2 / m) / (m - 1).  When T* is requested with maps, this kernel also
 // stores it (for every sample, in or out of the map).
-// SINGLE: the channel groups with a channel that has no polynomials (an
-// expm1 per sample; a kernel of its own, as its registers would halve the
-// other's blocks per CU).
 constexpr int kRdMapChan = 2, kRdMapThreads = kRdTile / 4;
-template <bool SINGLE>
-__device__ void map_item(const ReduceArgs& a, double* gsm, int p, int group) {
+__global__ __launch_bounds__(kRdMapThreads, 4) void k_rd_map(ReduceArgs a) {
+  extern __shared__ double gsm[];
+  const int p = blockIdx.x % a.P, group = blockIdx.x / a.P;   // a group's blocks share M rows
   const int C = a.map_n * a.map_n, tid = threadIdx.x;
   double2* const v = (double2*)gsm;                   // [tile] both channels
   double2* const s1 = v + kRdTile;                    // [C]
@@ -464,36 +318,26 @@ __device__ void map_item(const ReduceArgs& a, double* gsm, int p, int group) {
     cnt[c] = 0u;
     s1[c] = s2[c] = make_double2(0.0, 0.0);
   }
-  const RdConst poly = (RdConst)(uintptr_t)a.poly;
-  const double dth = a.theta0 + a.dtheta[p];
-  double lz[kRdMapChan], cr[kRdMapChan][kRdTerms], shift[kRdMapChan];
+  double lz[kRdMapChan], shift[kRdMapChan];
   const float* row[kRdMapChan];
   const double* Mr[kRdMapChan];
+  const double* const csc = a.csc_grid + p * a.T;
+  auto t_star = [&](int q, double c, float d, double M) {
+    const double em = expm1(lz[q] * c);     // eta - 1
+    return ((double)d + em * M) / (1.0 + em);
+  };
 #pragma unroll
   for (int q = 0; q < kRdMapChan; ++q) {
     const int kq = min(kl0 + q, a.kg - 1), k = a.k0 + kq;   // dead slots repeat the last channel
     lz[q] = a.lnz[k];
     row[q] = a.tod + ((int64_t)p * a.K + k) * a.ld;
     Mr[q] = a.M + (int64_t)kq * a.T;
-#pragma unroll
-    for (int n = 0; n < kRdTerms; ++n) cr[q][n] = poly[k * kRdPoly + n];
-  }
-  const double mid = a.range[0], inv = a.range[1];
-  const double xp = (a.dtheta[p] - mid) * inv;
-  auto t_star = [&](int q, double th, double x, double csc, double d, double M) {
-    if constexpr (!SINGLE) return fma(poly_at(cr[q], x), d - M, d);
-    const double em = expm1(lz[q] * csc);     // eta - 1
-    return (d + em * M) / (1.0 + em);
-  };
-#pragma unroll
-  for (int q = 0; q < kRdMapChan; ++q) {
-    const double th = a.scan_th[0];
-    shift[q] = t_star(q, th, fma(th, inv, xp), 1.0 / sin(th + dth), row[q][0], Mr[q][0]);
+    shift[q] = t_star(q, csc[0], row[q][0], Mr[q][0]);
   }
   float* const out_ts = a.t_star ? a.t_star + ((int64_t)p * a.K + a.k0 + kl0) * a.ld : nullptr;
   const int tiles = (int)((a.T + kRdTile - 1) / kRdTile);
   float d[kRdMapChan][4];
-  double M[kRdMapChan][4], th[4];
+  double M[kRdMapChan][4], c4[4];
   // a tile's run list: its first 2 runs per thread (what most tiles have),
   // the samples' places, the number of runs
   uint32_t u0, u1;
@@ -513,7 +357,7 @@ __device__ void map_item(const ReduceArgs& a, double* gsm, int p, int group) {
       load4<Float4, true>(row[q] + t, nt, d[q]);
       load4<Double4>(Mr[q] + t, nt, M[q]);
     }
-    load4<Double4>(a.scan_th + t, nt, th);
+    load4<Double4>(csc + t, nt, c4);
   };
   load(0);
   __syncthreads();
@@ -525,12 +369,10 @@ __device__ void map_item(const ReduceArgs& a, double* gsm, int p, int group) {
       float o[kRdMapChan][4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const double x = fma(th[i], inv, xp);
-        const double csc = SINGLE ? 1.0 / sin(th[i] + dth) : 0.0;
         double ts[kRdMapChan];
 #pragma unroll
         for (int q = 0; q < kRdMapChan; ++q) {
-          ts[q] = t_star(q, th[i], x, csc, d[q][i], M[q][i]);
+          ts[q] = t_star(q, c4[i], d[q][i], M[q][i]);
           o[q][i] = (float)ts[q];
         }
         v[i * kRdMapThreads + tid] = make_double2(ts[0] - shift[0], ts[1] - shift[1]);
@@ -557,8 +399,8 @@ __device__ void map_item(const ReduceArgs& a, double* gsm, int p, int group) {
           if (e + g >= len) y[g] = make_double2(0.0, 0.0);
           x1.x += y[g].x;
           x1.y += y[g].y;
-          x2.x = fma(y[g].x, y[g].x, x2.x);
-          x2.y = fma(y[g].y, y[g].y, x2.y);
+          x2.x = add_square(x2.x, y[g].x);
+          x2.y = add_square(x2.y, y[g].y);
         }
       }
       if (u >> 28) {
@@ -593,28 +435,6 @@ __device__ void map_item(const ReduceArgs& a, double* gsm, int p, int group) {
       }
       out[c] = make_double2(w, mean);
     }
-  }
-}
-
-template <bool SINGLE>
-__global__ __launch_bounds__(kRdMapThreads, SINGLE ? 2 : 4) void k_rd_map(ReduceArgs a) {
-  extern __shared__ double gsm[];
-  const RdConst poly = (RdConst)(uintptr_t)a.poly;
-  const int groups = (a.kg + kRdMapChan - 1) / kRdMapChan;
-  const int items = groups * a.P;
-  if constexpr (SINGLE) {
-    bool any = false;
-    for (int k = threadIdx.x; k < a.kg; k += kRdMapThreads)
-      any |= a.poly[(a.k0 + k) * kRdPoly + 2 * kRdTerms] != 0.0;
-    if (!__syncthreads_or(any)) return;
-  }
-  for (int item = blockIdx.x; item < items; item += gridDim.x) {
-    const int p = item % a.P, group = item / a.P;   // a group's blocks share M rows
-    bool single = false;
-    for (int q = 0; q < kRdMapChan; ++q)
-      single |= poly[(a.k0 + min(group * kRdMapChan + q, a.kg - 1)) * kRdPoly + 2 * kRdTerms] != 0.0;
-    if (single == SINGLE) map_item<SINGLE>(a, gsm, p, group);
-    __syncthreads();
   }
 }
 
@@ -722,6 +542,9 @@ __global__ __launch_bounds__(kRdThreads) void k_rd_combine(ReduceArgs a) {
 void launch_reduce_setup(const ReduceArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_rd_scan, dim3((unsigned)((a.T + kRdThreads - 1) / kRdThreads)),
                      dim3(kRdThreads), 0, s, a);
+  if (a.csc_common)
+    hipLaunchKernelGGL(k_rd_csc, dim3((unsigned)((a.T + kRdThreads - 1) / kRdThreads), a.P),
+                       dim3(kRdThreads), 0, s, a);
   hipLaunchKernelGGL(k_rd_pwv_mean, dim3(1), dim3(kRdThreads), 0, s, a);
   hipLaunchKernelGGL(k_rd_channel, dim3(a.K), dim3(kRdThreads), 0, s, a);
   if (a.runs)
@@ -731,7 +554,7 @@ void launch_reduce_setup(const ReduceArgs& a, hipStream_t s) {
 
 void launch_reduce_common(const ReduceArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_rd_common,
-                     dim3((unsigned)((a.T + 4 * kRdThreads - 1) / (4 * kRdThreads)),
+                     dim3((unsigned)((a.T + kRdThreads - 1) / kRdThreads),
                           (a.kg + kRdChan - 1) / kRdChan),
                      dim3(kRdThreads), 0, s, a);
 }
@@ -740,13 +563,11 @@ int launch_reduce_grid(const ReduceArgs& a, hipStream_t s) {
   const int C = a.map_n * a.map_n;
   if (a.runs) {
     const size_t lds = (size_t)C * 32 + (size_t)((C + 3) & ~3) * 4 + kRdTile * (16 + 2);
-    for (const void* k : {(const void*)k_rd_map<false>, (const void*)k_rd_map<true>})
-      if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-        return 1;
-    const int items = (a.kg + kRdMapChan - 1) / kRdMapChan * a.P;
-    hipLaunchKernelGGL(k_rd_map<false>, dim3((unsigned)items), dim3(kRdMapThreads), lds, s, a);
-    hipLaunchKernelGGL(k_rd_map<true>, dim3((unsigned)std::min(items, 512)), dim3(kRdMapThreads),
-                       lds, s, a);
+    if (hipFuncSetAttribute((const void*)k_rd_map,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+      return 1;
+    const int groups = (a.kg + kRdMapChan - 1) / kRdMapChan;
+    hipLaunchKernelGGL(k_rd_map, dim3((unsigned)(a.P * groups)), dim3(kRdMapThreads), lds, s, a);
     return 0;
   }
   const size_t lds = (size_t)C * (2 * kRdGridChan * sizeof(double) + sizeof(unsigned));

@@ -1272,10 +1272,9 @@ gtod_status gtod_reduce(gtod_ctx* c, const gtod_reduce_desc* d, void* hip_stream
   if (kg < 1) return fail(c, GTOD_EINVAL, "workspace too small for one channel of the reduction");
   // scratch of the faster kernels, where there is room for it as well
   const int64_t tiles = (T + kRdTile - 1) / kRdTile;
-  const int64_t poly = round_up(K * kRdPoly * 8, 256);
-  const int64_t range = round_up((2 + 2 * ((T + 255) / 256)) * 8, 256);
+  const int64_t csc = round_up((int64_t)P * T * 8, 256);
   const int64_t runs = maps ? (int64_t)P * tiles * kRdTile * 6 + round_up((int64_t)P * tiles * 4, 256) : 0;
-  const int64_t extra = poly + range + runs;
+  const int64_t extra = (maps ? 2 : 1) * csc + runs;
   bool fast = avail > extra;
   if (fast && maps) {
     const int64_t n = (avail - extra - 256) / per_ch;
@@ -1334,10 +1333,10 @@ gtod_status gtod_reduce(gtod_ctx* c, const gtod_reduce_desc* d, void* hip_stream
   a.weight = d->weight;
   char* grp = ws + fixed;
   if (fast) {
-    a.poly = (double*)grp;
-    a.range = (double*)(grp + poly);
+    a.csc_common = (double*)grp;
     if (maps) {
-      a.runs = (uint32_t*)(grp + poly + range);
+      a.csc_grid = (double*)(grp + csc);
+      a.runs = (uint32_t*)(grp + 2 * csc);
       a.perm = (uint16_t*)(a.runs + (int64_t)P * tiles * kRdTile);
       a.n_runs = (int*)(a.perm + (int64_t)P * tiles * kRdTile);
     }

@@ -1,7 +1,7 @@
 """Common mode and maps at the edges of their kernels' ranges: tiles and tails
 of time, an odd channel left over, rows at any alignment, cells of one run and
-of many, elevation ranges with and without polynomials, workspaces with and
-without room for the run lists.
+of many, narrow and wide elevation ranges, workspaces with and without room for
+the run lists.
 
 Tolerances: T* within 2^-23 of itself (FP32 storage) + 1e-10 of the terms that
 cancel; maps within 1e-9 of those, weights 1e-8 relative (FP64 throughout)."""
@@ -24,7 +24,7 @@ def scenario(scan, T, K):
     sc = hex_scenario(T=max(T, 8), F=200, K=K)
     if scan == "stare":
         sc.scan = Scan("stare", theta0=sc.scan.theta0)
-    elif scan == "wide":          # several degrees: no polynomial of degree 6
+    elif scan == "wide":          # several degrees
         t = np.arange(max(T, 8)) / sc.f_sample_hz
         traj = np.stack([0.08 * np.cos(3 * t), 0.08 * np.sin(5 * t)], axis=1)
         sc.scan = Scan("traj", theta0=sc.scan.theta0, traj=np.ascontiguousarray(traj))

@@ -207,6 +207,7 @@ struct ReduceArgs {
   int64_t pwv_ld, pwv_len;
   double pwv_host;            // used when pwv is null
   double* pwv_mean;           // scratch [1]
+  double* pwv_part;           // scratch [256], or null: partial sums of pwv
   double* lnz;                // scratch [K] ln of the channel zenith transmission
   double* scan_phi;           // scratch [T]
   double* scan_th;            // scratch [T]

@@ -1274,7 +1274,8 @@ gtod_status gtod_reduce(gtod_ctx* c, const gtod_reduce_desc* d, void* hip_stream
   const int64_t tiles = (T + kRdTile - 1) / kRdTile;
   const int64_t csc = round_up((int64_t)P * T * 8, 256);
   const int64_t runs = maps ? (int64_t)P * tiles * kRdTile * 6 + round_up((int64_t)P * tiles * 4, 256) : 0;
-  const int64_t extra = (maps ? 2 : 1) * csc + runs;
+  const int64_t parts = 256 * 8;
+  const int64_t extra = (maps ? 2 : 1) * csc + runs + parts;
   bool fast = avail > extra;
   if (fast && maps) {
     const int64_t n = (avail - extra - 256) / per_ch;
@@ -1340,6 +1341,7 @@ gtod_status gtod_reduce(gtod_ctx* c, const gtod_reduce_desc* d, void* hip_stream
       a.perm = (uint16_t*)(a.runs + (int64_t)P * tiles * kRdTile);
       a.n_runs = (int*)(a.perm + (int64_t)P * tiles * kRdTile);
     }
+    a.pwv_part = (double*)(grp + extra - parts);
     grp += extra;
   }
   a.M = maps ? (double*)grp : nullptr;

@@ -83,3 +83,28 @@ def test_maps_and_common_mode(scan, half, T, K, n, pad, room):
         check_tstar(sc, d.cpu().numpy()[:, :, :T], t_b, 1.1, 30 * ARC)
     finally:
         g.free(ctx)
+
+
+@pytest.mark.parametrize("length,pad", [(1, 0), (40, 3), (9362, 1), (9363, 0), (30001, 7)])
+def test_mean_pwv_of_the_partial_sums(length, pad):
+    """7 rows of PWV around one tile of the partial sums (65536 values) and
+    over several, contiguous and pitched: the same bits as summed by one block,
+    where the workspace has no room for the partial sums."""
+    sc = scenario("daisy", 64, 3)
+    r = np.random.default_rng(length)
+    pwv = torch.full((7, length + pad), float("nan"), device="cuda")
+    pwv[:, :length] = torch.from_numpy(r.uniform(0.8, 1.3, (7, length)).astype(np.float32))
+    got = []
+    for ws in (8 << 20, 4096):
+        ctx = new_ctx(workspace_bytes=ws)
+        try:
+            run = g.ScenarioRun(ctx, sc)
+            _, d = fields(sc, 64, 64)
+            ts = torch.zeros_like(d)
+            desc = run.reduce_desc(d, 30 * ARC, t_star=ts, pwv=pwv)
+            desc.pwv_len = length
+            g.reduce(ctx, desc)
+            got.append(ts.cpu())
+        finally:
+            g.free(ctx)
+    assert torch.isfinite(got[0]).all() and torch.equal(got[0], got[1])

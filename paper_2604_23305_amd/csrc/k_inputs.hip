@@ -22,6 +22,7 @@
 #include <cmath>
 
 #include "gtod_internal.h"
+#include "lds_barrier.h"
 
 namespace gtod {
 
@@ -188,7 +189,7 @@ __global__ __launch_bounds__(64) void k_screen_weights(ScreenConvArgs a) {
 // read or written per cell).  512 x 65536 cells of 0.2 m under a 5 m dish (1961
 // cells of footprint): 19.1 ms when every output summed its whole disk from a
 // 2-D tile, 1.46 ms with branches on the widths instead of partial sums in LDS,
-// 0.92 ms now; error against the exact sum 3.4e-16 rms (1.1e-15 before).
+// 0.84 ms now; error against the exact sum 3.4e-16 rms (1.1e-15 before).
 template <int N>
 __global__ __launch_bounds__(256) void k_screen_conv(ScreenConvArgs a) {
   __shared__ double buf[2][256 + 2 * N];
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(256) void k_screen_conv(ScreenConvArgs a) {
     b[tid] = va;
     if (two) b[256 + tid] = vb;
     load(y + 1);
-    __syncthreads();
+    lds_barrier();
     const double* const s = b + N + tid;
     double h = lane_value(gx, 0) * s[0];
     partial[0][tid] = h;
@@ -265,10 +266,12 @@ int launch_source_conv(const SrcConvArgs& a, hipStream_t s) {
 void launch_screen_conv(const ScreenConvArgs& a0, hipStream_t s) {
   ScreenConvArgs a = a0;
   hipLaunchKernelGGL(k_screen_weights, dim3(1), dim3(64), 0, s, a);
-  // strips long enough that their ry extra rows on either side cost little,
-  // unless that leaves the card idle
+  // the longest strips (their ry extra rows on either side are work done
+  // again) that still give every CU the two workgroups it holds: 512 x 65536
+  // cells of 0.2 m 0.92 -> 0.84 ms against four workgroups, 300 x 8000 of 0.25 m
+  // 299 -> 217 us
   const int64_t cols = (a.nx + 255) / 256;
-  const int64_t strips = std::max<int64_t>(1, 1024 / cols);
+  const int64_t strips = std::max<int64_t>(1, 512 / cols);
   a.strip = (int)std::max<int64_t>((a.ny + strips - 1) / strips, 16);
   const dim3 grid((unsigned)cols, (unsigned)((a.ny + a.strip - 1) / a.strip));
   const int n = std::max(a.rx, a.ry);

@@ -306,24 +306,31 @@ void launch_tile_responses(const float* B, int* e0, int* e1, double* unit0, doub
 // Contraction
 // ---------------------------------------------------------------------------
 
-template <bool F16, int WR, int WC, int NI, int NJ, int STAGES>
-__global__ __launch_bounds__(256, 1) void k_contract(GemmArgs a) {
+// SPL = 2: two waves per 32 x 32 tile, one for each accumulator (C0; C1 with
+// C2).  Where a launch leaves most CUs idle its time is a wave's chain of LDS
+// reads, splits and MFMAs per step: 160 rows x 347 channels x 3000 bins take 50
+// us in 64 x 32 tiles so (57 with one wave per tile, 62 in 64 x 64 tiles; 32 x
+// 32 tiles and 16 stages are no faster).  The sums are the same.
+template <bool F16, int WR, int WC, int NI, int NJ, int STAGES, int SPL = 1>
+__global__ __launch_bounds__(64 * WR * WC * SPL, 1) void k_contract(GemmArgs a) {
   typedef Half<F16> H;
   typedef typename H::v8 v8;
   constexpr int NPL = H::kPlanes, ND = H::kOps;
-  constexpr int MT = WR * 32 * NJ, NT = WC * 32 * NI, NG = NT / kGroup;
+  constexpr int MT = WR * 32 * NJ, NT = WC * 32 * NI, NG = NT < kGroup ? 1 : NT / kGroup;
   constexpr int kPanelBytes = MT * KC * 4;
   constexpr int kGroupBytes = NPL * kPlaneBytes;
-  constexpr int kStageBytes = kPanelBytes + NG * kGroupBytes;
+  // a tile of 32 channels takes half of each plane of its group
+  constexpr int kPlane = NT < kGroup ? kPlaneBytes / 2 : kPlaneBytes;
+  constexpr int kStageBytes = kPanelBytes + NG * NPL * kPlane;
   constexpr int kDma = kStageBytes / 1024;         // 1 KB DMAs of a stage
-  constexpr int kPanelQ = MT / 16 / 4;             // panel DMAs per wave
-  constexpr int Q = (kDma + 3) / 4;                // DMAs per wave (some one less)
-  constexpr int NPROD = first_slot<F16>(NPL);
-  static_assert(WR * WC == 4 && NT % kGroup == 0 && (MT / 16) % 4 == 0, "shape");
+  constexpr int kTiles = WR * WC, NW = kTiles * SPL;
+  constexpr int kPanelQ = MT / 16 / 4;             // panel DMAs per wave (SPL = 1)
+  constexpr int Q = (kDma + NW - 1) / NW;          // DMAs per wave (some one less)
+  static_assert(SPL > 1 || (kTiles == 4 && NT % kGroup == 0 && (MT / 16) % 4 == 0), "shape");
   static_assert((STAGES & (STAGES - 1)) == 0 && STAGES >= 4, "stage index by mask");
     // the ring, then the epilogue's slices
-  constexpr int kLds = STAGES * kStageBytes > 4 * epi_wave_bytes(NI)
-                           ? STAGES * kStageBytes : 4 * epi_wave_bytes(NI);
+  constexpr int kLds = STAGES * kStageBytes > kTiles * epi_wave_bytes(NI)
+                           ? STAGES * kStageBytes : kTiles * epi_wave_bytes(NI);
   static_assert(kLds <= 160 * 1024, "LDS");
 
   const int b = blockIdx.x;
@@ -358,7 +365,8 @@ __global__ __launch_bounds__(256, 1) void k_contract(GemmArgs a) {
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int h = lane >> 5, c = lane & 31;
-  const int rw = wave % WR, cw = wave / WR;
+  const int part = wave / kTiles;        // accumulator of this wave (SPL = 2)
+  const int rw = wave % WR, cw = wave % kTiles / WR;
 
   const int64_t Fp = a.Fp;
   const int n_steps = a.Fp / KC;
@@ -368,31 +376,41 @@ __global__ __launch_bounds__(256, 1) void k_contract(GemmArgs a) {
   // 1 KB blocks w + 4 q of a stage; a panel block is 16 rows, lane taking
   // bin quad (lane % 4) ^ swz(row) of row lane / 4.
   const char* const gp = reinterpret_cast<const char*>(a.panel + row0 * Fp);
-  uint32_t vp[kPanelQ];
-#pragma unroll
-  for (int q = 0; q < kPanelQ; ++q) {
-    const int r = (wave + 4 * q) * 16 + (lane >> 2);
-    const int64_t gr = min(row0 + r, n_rows - 1);
-    vp[q] = (uint32_t)(4 * ((gr - row0) * Fp + 4 * ((lane & 3) ^ swz(r))));
-  }
-  const char* gt[Q - kPanelQ];
   const int n_g = (a.Kp + kGroup - 1) / kGroup;
-#pragma unroll
-  for (int q = 0; q < Q - kPanelQ; ++q) {
-    const int e = min(wave + 4 * q, NG * NPL * 2 - 1);
+  auto panel_offset = [&](int block) {
+    const int r = block * 16 + (lane >> 2);
+    const int64_t gr = min(row0 + r, n_rows - 1);
+    return (uint32_t)(4 * ((gr - row0) * Fp + 4 * ((lane & 3) ^ swz(r))));
+  };
+  auto response = [&](int block) {
+    if constexpr (NT < kGroup)
+      return reinterpret_cast<const char*>(F16 ? a.Th : a.Tb) +
+             (size_t)(ch0 / kGroup) * n_steps * kGroupBytes + min(block, NPL - 1) * kPlaneBytes +
+             ch0 % kGroup * (KC * 2);
+    const int e = min(block, NG * NPL * 2 - 1);
     const int gr = min(ch0 / kGroup + e / (NPL * 2), n_g - 1);   // past the last: unused data
-    gt[q] = reinterpret_cast<const char*>(F16 ? a.Th : a.Tb) +
-            (size_t)gr * n_steps * kGroupBytes + (e % (NPL * 2)) * 1024;
+    return reinterpret_cast<const char*>(F16 ? a.Th : a.Tb) +
+           (size_t)gr * n_steps * kGroupBytes + (e % (NPL * 2)) * 1024;
+  };
+  // lane offset, source and advance per step of the wave's DMAs: the panel's
+  // first kPanelQ of each wave, or with SPL = 2 the first of the first waves
+  uint32_t vo[Q];
+  const char* src[Q];
+  uint32_t advance[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int block = wave + NW * q;
+    const bool panel = SPL == 1 ? q < kPanelQ : block < MT / 16;
+    vo[q] = panel ? panel_offset(block) : (uint32_t)lane * 16u;
+    src[q] = panel ? gp : response(block - MT / 16);
+    advance[q] = panel ? KC * 4 : kGroupBytes;
   }
-  const uint32_t vt = (uint32_t)lane * 16u;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(ring));
-  const bool all_q = kDma % 4 == 0 || wave < kDma % 4;   // this wave issues Q DMAs
+  const bool all_q = kDma % NW == 0 || wave < kDma % NW;   // this wave issues Q DMAs
   // DMA q of step st
   auto issue = [&](int st, int q) {
-    const uint32_t dst = lds0 + (uint32_t)((st & (STAGES - 1)) * kStageBytes + (wave + 4 * q) * 1024);
-    if (q < kPanelQ) dma16(gp + (size_t)st * (KC * 4), vp[q < kPanelQ ? q : 0], dst);
-    else if (q + 1 < Q || all_q)
-      dma16(gt[q < kPanelQ ? 0 : q - kPanelQ] + (size_t)st * kGroupBytes, vt, dst);
+    const uint32_t dst = lds0 + (uint32_t)((st & (STAGES - 1)) * kStageBytes + (wave + NW * q) * 1024);
+    if (q + 1 < Q || all_q) dma16(src[q] + (size_t)st * advance[q], vo[q], dst);
   };
   // wait until at most the wave's DMAs of STAGE_N stages are in flight
   auto wait_stages = [&](auto stage_n) {
@@ -430,8 +448,12 @@ __global__ __launch_bounds__(256, 1) void k_contract(GemmArgs a) {
   else wait_vm<0>();
   __builtin_amdgcn_s_barrier();
 
-  auto run = [&](auto nl_c) {
+  auto run = [&](auto nl_c, auto part_c) {
     constexpr int NL = decltype(nl_c)::value;
+    // planes of this wave
+    constexpr int P0 = SPL == 1 ? 0 : (decltype(part_c)::value ? 2 : 0);
+    constexpr int P1 = SPL == 1 ? NPL : (decltype(part_c)::value ? NPL : 2);
+    constexpr int kSlots = first_slot<F16>(P1) - first_slot<F16>(P0);
     if constexpr (NL == 0) {
       // no live channel: this wave only moves its part of the operands
       for (int s = 0; s < n_steps; ++s) {
@@ -444,18 +466,18 @@ __global__ __launch_bounds__(256, 1) void k_contract(GemmArgs a) {
         }
       }
     } else {
-      constexpr int NM = NPROD * NL * NJ;              // slots of a step
+      constexpr int NM = kSlots * NL * NJ;             // slots of a step
       constexpr int kConv0 = NM / 5 > 3 ? NM / 5 : 3;  // first split slot
       constexpr int kConvS = (NM - kConv0) / (4 * NJ) > 0 ? (NM - kConv0) / (4 * NJ) : 1;
       typedef v8 Ops[NJ][ND];
-      v8 pf[2][NL];           // response planes 0 and 1 of the coming step
+      v8 pf[2][NL];           // the first two response planes of the coming step
       float4 raw[NJ][2];
       auto read_x = [&](const char* st, int r) {
         raw[r >> 1][r & 1] = *reinterpret_cast<const float4*>(
             st + (oP ^ (16 * (r & 1))) + (r >> 1) * 32 * KC * 4);
       };
       auto read_b = [&](const char* st, int p, int i) {
-        return *reinterpret_cast<const v8*>(st + oB + (i >> 1) * kGroupBytes + p * kPlaneBytes +
+        return *reinterpret_cast<const v8*>(st + oB + (i >> 1) * kGroupBytes + p * kPlane +
                                             (i & 1) * 32 * KC * 2);
       };
       // pair k of the 4 NJ pairs: row tile k / 4, bins 2 (k % 4), + 1
@@ -481,10 +503,10 @@ __global__ __launch_bounds__(256, 1) void k_contract(GemmArgs a) {
 #pragma unroll
         for (int p = 0; p < 2; ++p)
 #pragma unroll
-          for (int i = 0; i < NL; ++i) bp[p][i] = pf[p][i];
+          for (int i = 0; i < NL; ++i) bp[P0 + p][i] = pf[p][i];
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int p = 0; p < NPL; ++p)
+        for (int p = P0; p < P1; ++p)
 #pragma unroll
           for (int m = 0; m < n_products<F16>(p); ++m)
 #pragma unroll
@@ -492,13 +514,13 @@ __global__ __launch_bounds__(256, 1) void k_contract(GemmArgs a) {
 #pragma unroll
               for (int j = 0; j < NJ; ++j) {
                 const int u = (m * NL + i) * NJ + j;
-                const int t = first_slot<F16>(p) * NL * NJ + u;
+                const int t = (first_slot<F16>(p) - first_slot<F16>(P0)) * NL * NJ + u;
                 f32x16& d = acc[acc_of(p)][i][j];
                 d = H::mfma(bp[p][i], cur[j][op_of(p, m)], d);
                 // responses two planes ahead
                 if (u < NL) {
-                  if (p + 2 < NPL) bp[p + 2][u] = read_b(st, p + 2, u);
-                  else bp[p + 2][u] = read_b(sn, p + 2 - NPL, u);
+                  if (p + 2 < P1) bp[p + 2][u] = read_b(st, p + 2, u);
+                  else bp[p + 2][u] = read_b(sn, p + 2 - P1 + P0, u);
                 }
                 if (t < 2 * NJ) read_x(sn, t);
                 if (kMain && t < Q) issue(s + STAGES - 1, t);
@@ -515,13 +537,13 @@ __global__ __launch_bounds__(256, 1) void k_contract(GemmArgs a) {
 #pragma unroll
         for (int p = 0; p < 2; ++p)
 #pragma unroll
-          for (int i = 0; i < NL; ++i) pf[p][i] = bp[NPL + p][i];
+          for (int i = 0; i < NL; ++i) pf[p][i] = bp[P1 + p][i];
       };
       Ops xa, xb;
 #pragma unroll
       for (int p = 0; p < 2; ++p)
 #pragma unroll
-        for (int i = 0; i < NL; ++i) pf[p][i] = read_b(ring, p, i);
+        for (int i = 0; i < NL; ++i) pf[p][i] = read_b(ring, P0 + p, i);
 #pragma unroll
       for (int r = 0; r < 2 * NJ; ++r) read_x(ring, r);
 #pragma unroll
@@ -539,12 +561,30 @@ __global__ __launch_bounds__(256, 1) void k_contract(GemmArgs a) {
       }
     }
   };
-  if (NI >= 4 && n_live == 4) run(std::integral_constant<int, NI >= 4 ? 4 : 1>{});
-  else if (NI >= 4 && n_live == 3) run(std::integral_constant<int, NI >= 4 ? 3 : 1>{});
-  else if (NI >= 2 && n_live == 2) run(std::integral_constant<int, NI >= 2 ? 2 : 1>{});
-  else if (WC == 1 || n_live >= 1) run(std::integral_constant<int, 1>{});
-  else run(std::integral_constant<int, 0>{});
+  auto run_part = [&](auto part_c) {
+    if (NI >= 4 && n_live == 4) run(std::integral_constant<int, NI >= 4 ? 4 : 1>{}, part_c);
+    else if (NI >= 4 && n_live == 3) run(std::integral_constant<int, NI >= 4 ? 3 : 1>{}, part_c);
+    else if (NI >= 2 && n_live == 2) run(std::integral_constant<int, NI >= 2 ? 2 : 1>{}, part_c);
+    else if (WC == 1 || n_live >= 1) run(std::integral_constant<int, 1>{}, part_c);
+    else run(std::integral_constant<int, 0>{}, part_c);
+  };
+  if (SPL == 1 || part == 0) run_part(std::integral_constant<int, 0>{});
+  else run_part(std::integral_constant<int, SPL - 1>{});
   __syncthreads();   // every wave is done with the ring before the epilogue reuses it
+  if constexpr (SPL > 1) {
+    // C1 to the wave that has C0, past the epilogue's slices
+    static_assert(NI * NJ == 1 && kTiles * (epi_wave_bytes(NI) + 4096) <= kLds, "exchange");
+    float* const x = reinterpret_cast<float*>(ring + kLds - kTiles * 4096) +
+                     wave % kTiles * 1024 + lane;
+    if (part) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) x[e * 64] = acc[1][0][0][e];
+    }
+    __syncthreads();
+    if (part) return;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[1][0][0][e] = x[e * 64];
+  }
   if (n_live == 0) return;
   char* const spk = ring + wave * epi_wave_bytes(NI);
   const int64_t row_w = row0 + rw * 32 * NJ;
@@ -623,13 +663,13 @@ __global__ __launch_bounds__(256, 1) void k_contract(GemmArgs a) {
 
 namespace {
 
-template <bool F16, int WR, int WC, int NI, int NJ, int STAGES>
+template <bool F16, int WR, int WC, int NI, int NJ, int STAGES, int SPL = 1>
 void launch_shape(GemmArgs a, hipStream_t s) {
   constexpr int MT = WR * 32 * NJ, NT = WC * 32 * NI;
   const int64_t n_tt = ((int64_t)a.n_pix * a.Tpad + MT - 1) / MT;
   a.n_cg = (a.K + NT - 1) / NT;
-  hipLaunchKernelGGL((k_contract<F16, WR, WC, NI, NJ, STAGES>),
-                     dim3((unsigned)(round_up(n_tt, 8) * a.n_cg)), dim3(256), 0, s, a);
+  hipLaunchKernelGGL((k_contract<F16, WR, WC, NI, NJ, STAGES, SPL>),
+                     dim3((unsigned)(round_up(n_tt, 8) * a.n_cg)), dim3(64 * WR * WC * SPL), 0, s, a);
 }
 
 // One workgroup of a shape runs on a CU at a time (two of the 128 x 64
@@ -638,25 +678,29 @@ void launch_shape(GemmArgs a, hipStream_t s) {
 // with one round on an idle card (FP16 halves; BF16).  In launches of many
 // rounds 256 x 128 is the fastest per output: 43.2 ms of contractions in six
 // minutes of the 49-pixel, 347-channel IFU, against 47.4 with 256 x 64 and
-// 48.2 with 128 x 64; a launch of 160 rows takes 57 us with 64 x 64 tiles
-// against 261 with 256 x 128.  Up to 64 channels half of a 256 x 128 tile
+// 48.2 with 128 x 64; a launch of 160 rows takes 62 us with 64 x 64 tiles
+// against 261 with 256 x 128, and 50 with 64 x 32; but 198 workgroups of 64 x 32
+// take 78 where 108 of 64 x 64 take 65 (operands from beyond the L2), so they
+// count by rounds of 128.  Up to 64 channels half of a 256 x 128 tile
 // would be dead.
 struct Shape {
-  int rows, channels;
+  int rows, channels, round;
   float f16_us, bf16_us;
 };
-constexpr Shape kShapes[4] = {
-    {256, 128, 270.f, 210.f}, {256, 64, 150.f, 127.f}, {128, 64, 92.f, 85.f}, {64, 64, 58.f, 58.f}};
+constexpr int kNShapes = 5;
+constexpr Shape kShapes[kNShapes] = {{256, 128, 256, 270.f, 210.f}, {256, 64, 256, 150.f, 127.f},
+                                     {128, 64, 256, 92.f, 85.f},    {64, 64, 256, 58.f, 58.f},
+                                     {64, 32, 128, 46.f, 41.f}};
 
 template <bool F16>
 void launch_contract(const GemmArgs& a, hipStream_t s) {
   const int64_t rows = (int64_t)a.n_pix * a.Tpad;
   int best = -1;
   float least = 0.f;
-  for (int q = a.K <= 64 ? 1 : 0; q < 4; ++q) {
+  for (int q = a.K <= 64 ? 1 : 0; q < kNShapes; ++q) {
     const Shape& h = kShapes[q];
     const int64_t wgs = (rows + h.rows - 1) / h.rows * ((a.K + h.channels - 1) / h.channels);
-    const float us = (float)((wgs + 255) / 256) * (F16 ? h.f16_us : h.bf16_us);
+    const float us = (float)((wgs + h.round - 1) / h.round) * (F16 ? h.f16_us : h.bf16_us);
     if (best < 0 || us < least) {
       best = q;
       least = us;
@@ -666,7 +710,8 @@ void launch_contract(const GemmArgs& a, hipStream_t s) {
     case 0: launch_shape<F16, 4, 1, 4, 2, 4>(a, s); break;
     case 1: launch_shape<F16, 4, 1, 2, 2, 4>(a, s); break;
     case 2: launch_shape<F16, 2, 2, 1, 2, 4>(a, s); break;
-    default: launch_shape<F16, 2, 2, 1, 1, 8>(a, s); break;
+    case 3: launch_shape<F16, 2, 2, 1, 1, 8>(a, s); break;
+    default: launch_shape<F16, 2, 1, 1, 1, 8, 2>(a, s); break;
   }
 }
 

@@ -49,7 +49,9 @@ def _near_reference(sc):
     (40, 90, 5, 4990),     # three live 32-tiles, a last half tile of rows
     (64, 64, 5, 4990),     # 256 x 64 tiles
     (96, 31, 5, 4990),     # the same with one live 32-tile
-    (40, 129, 1, 65),      # 64 x 64 tiles, the last of padding rows
+    (40, 129, 5, 500),     # 64 x 64 tiles
+    (40, 129, 1, 65),      # 64 x 32 tiles, the last of padding rows
+    (48, 33, 1, 200),      # the same, both halves of a response group
     (200, 64, 3, 63),
 ])
 def test_tile_shapes_match_oracle_and_each_other(ctx, F, K, P, T, prec):

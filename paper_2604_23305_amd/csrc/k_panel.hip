@@ -224,11 +224,12 @@ __device__ __forceinline__ f32x4 row_deviation(const Bins& b, f32x4 t0, f32x4 t1
 // rr-th, over the passes of 1024 bins first, first + stride, ...  Within a
 // pass the spectra E, D, W, Pref stay in registers, and the cube corners
 // are loaded only where a row's cell is another than the row's before.
-// kBatch rows' table values are loaded together, ahead of their arithmetic.
+// kBatch rows' table values are loaded together, ahead of their arithmetic;
+// n_rows is a multiple of it.
+constexpr int kBatch = 2;
 template <class Rec>
 __device__ __forceinline__ void panel_rows(const PanelArgs& a, int n_rows, int first,
                                            int stride, Rec record) {
-  constexpr int kBatch = 2;
   const int64_t Fp = a.Fp;
   const int64_t ld = a.cube_ld, crow = (int64_t)a.n_az * a.cube_ld;
   uint32_t far = 0;
@@ -413,9 +414,12 @@ void launch_panel(const PanelArgs& a0, hipStream_t s) {
   // A workgroup per bin pass and fewer rows in each as long as that spreads the
   // rows more evenly over the card (us at 1750 bins, against 32 rows and all
   // passes in one: 33621 rows 90 / 106, 42000 109 / 119, 56000 135 / 146, 84000
-  // 200 / 206); in longer launches a row's record serves all its passes (526848
+  // 200 / 206; against 8 rows, 3000 bins: 160 rows 11.7 / 20.4, 2800 rows 30.8 /
+  // 36.2, at 7600 rows of 1500 bins no longer, 45.6 / 44.2); in longer launches a row's record serves all its passes (526848
   // rows of 3000 bins: 1.59 ms, 1.64 with one pass each).
-  a.rows_wg = rows < 1024 * kPanelRows ? 8 : (rows < 2048 * kPanelRows ? 16 : kPanelRows);
+  a.rows_wg = rows < 1024 ? 2 : rows < 4096 ? 4 : rows < 1024 * kPanelRows ? 8
+              : rows < 2048 * kPanelRows ? 16 : kPanelRows;
+  static_assert(2 % kBatch == 0, "rows per workgroup");
   const dim3 grid((unsigned)(rows / a.rows_wg), rows < 4096 * kPanelRows ? passes : 1);
   if (a.n_buckets <= 1) {
     hipLaunchKernelGGL(k_panel, grid, dim3(256), 0, s, a);

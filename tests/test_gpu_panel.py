@@ -65,13 +65,16 @@ def test_sorted_rows_match_rows_in_order(F, pitch, offset):
     assert e.max() <= max(1e-6, (F + 8) * 2.0 ** -24)
 
 
-@pytest.mark.parametrize("T", [4680, 4700, 9340, 9380, 18720])
-def test_every_spread_of_the_rows_gives_the_same_outputs(T):
-    """7 pixels on either side of 32768, 65536 and 131072 panel rows, two
-    passes of bins, in one window and in windows of 1792 samples."""
+@pytest.mark.parametrize("T,window", [
+    (4680, 1792), (4700, 1792), (9340, 1792), (9380, 1792), (18720, 1792),
+    (700, 512), (500, 128),   # 4 and 2 rows per workgroup in the windows
+])
+def test_every_spread_of_the_rows_gives_the_same_outputs(T, window):
+    """7 pixels on either side of 32768, 65536 and 131072 panel rows, and
+    below 4096 and 1024, two passes of bins, in one window and in several."""
     sc = tiny_scenario(F=1030, K=2, P=7, T=T, filt="matrix")
     got = []
-    for step in (T, 1792):
+    for step in (T, window):
         ctx = new_ctx()
         try:
             run = g.ScenarioRun(ctx, sc)

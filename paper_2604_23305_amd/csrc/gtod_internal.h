@@ -121,11 +121,11 @@ struct PinkArgs {
   int accumulate;
   int lgB2;              // log2 of the columns per pass-2 workgroup
   const float2* tab;     // [4096] e^{2 pi i m / 4096}
-  float2* tab_w;         // the same table, written by k_pink_tables
 };
 constexpr int kPinkLgM2 = 11;                // log2 of the usual 1/f pass-1 length
 constexpr int kPinkLgB2 = 4;                 // log2 of the 1/f pass-2 columns per workgroup
-constexpr int kPinkTableFloat2 = 2 * 4096;   // reserved at the workspace head
+constexpr int kPinkTable = 4096;             // twiddle table
+constexpr int kPinkTableFloat2 = 2 * 4096;   // of a workspace, before the series' scratch
 
 // setup kernels (FP64)
 struct SpecSetupArgs {
@@ -323,7 +323,7 @@ size_t tiled_response_bytes(int Kp, int Fp, bool f16);
 void launch_tile_responses(const float* B, int* e0, int* e1, double* unit0, double* unit1,
                            uint16_t* Tb, uint16_t* Th, int Kp, int Fp, int pexp,
                            hipStream_t s);
-void launch_pink_tables(const PinkArgs& a, hipStream_t s);
+void launch_pink_tables(float2* tab, hipStream_t s);
 void launch_pink_pass1(const PinkArgs& a, hipStream_t s);
 void launch_pink_pass2(const PinkArgs& a, hipStream_t s);
 void launch_philox(const uint32_t* ctr, uint32_t* out, int64_t n,

@@ -592,8 +592,9 @@ __global__ __launch_bounds__(256) void k_pink_pass2(PinkArgs a) {
   }
 }
 
-void launch_pink_tables(const PinkArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_pink_tables, dim3(kLdsC / 256), dim3(256), 0, s, a.tab_w);
+void launch_pink_tables(float2* tab, hipStream_t s) {
+  static_assert(kPinkTable == kLdsC, "table");
+  hipLaunchKernelGGL(k_pink_tables, dim3(kPinkTable / 256), dim3(256), 0, s, tab);
 }
 
 void launch_pink_pass1(const PinkArgs& a, hipStream_t s) {

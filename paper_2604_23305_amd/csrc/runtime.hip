@@ -65,26 +65,40 @@ constexpr size_t kSlotBytes = 1 << 20;
 // Device scratch of gtod_simulate_tod_noalloc: one copy per GPU, resident
 // from the library's first use on that device until the process ends.  In
 // host code this name is only a stand-in for the symbol; the device
-// address comes from hipGetSymbolAddress (scratch_address below).
+// address comes from hipGetSymbolAddress (device_statics below).
 static __device__ __align__(256) unsigned char scratch[GTOD_NOALLOC_SCRATCH_BYTES];
 
-std::mutex g_scratch_mu;
-std::map<int, void*> g_scratch_ptr;   // device -> address of its scratch
+// The 1/f transforms' twiddle table, one copy per GPU: written at the first
+// context's creation, before any use, and constant from then on.
+static __device__ float2 pink_table[kPinkTable];
 
-// Address of `scratch` on `dev`, which must be the current device; looked
-// up once per device.
-hipError_t scratch_address(int dev, void** out) {
-  std::lock_guard<std::mutex> lk(g_scratch_mu);
-  auto it = g_scratch_ptr.find(dev);
-  if (it != g_scratch_ptr.end()) {
+struct DeviceStatics {
+  void* scratch = nullptr;
+  const float2* pink_table = nullptr;
+};
+std::mutex g_statics_mu;
+std::map<int, DeviceStatics> g_statics;   // by device
+
+// The statics of `dev`, which must be the current device; looked up, and the
+// table written, once per device.
+hipError_t device_statics(int dev, DeviceStatics* out) {
+  std::lock_guard<std::mutex> lk(g_statics_mu);
+  auto it = g_statics.find(dev);
+  if (it != g_statics.end()) {
     *out = it->second;
     return hipSuccess;
   }
-  void* p = nullptr;
-  const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+  DeviceStatics d;
+  hipError_t e = hipGetSymbolAddress(&d.scratch, HIP_SYMBOL(scratch));
+  void* table = nullptr;
+  if (e == hipSuccess) e = hipGetSymbolAddress(&table, HIP_SYMBOL(pink_table));
   if (e != hipSuccess) return e;
-  g_scratch_ptr[dev] = p;
-  *out = p;
+  launch_pink_tables(static_cast<float2*>(table), nullptr);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if ((e = hipStreamSynchronize(nullptr)) != hipSuccess) return e;
+  d.pink_table = static_cast<const float2*>(table);
+  g_statics[dev] = d;
+  *out = d;
   return hipSuccess;
 }
 
@@ -108,6 +122,7 @@ struct gtod_ctx {
   int precision = GTOD_PREC_FP32;
   uint32_t flags = 0;
   uint64_t budget = 0, used = 0, ws_bytes = 0;
+  const float2* pink_table = nullptr;   // the device's
   double fs = 0, eta_taper = 0, rho_surf = 0, eta_pol = 0, delta_J = 0,
          eta_pb = 0, t_cmb = 0;
   std::map<int32_t, ScreenObj> screens;
@@ -240,11 +255,13 @@ static_assert(GTOD_NOALLOC_SCRATCH_BYTES % 256 == 0 &&
 // and every kernel writes what it later reads.  The pinned host slots and
 // their events are made here, so the call itself allocates nothing.
 gtod_status init_noalloc(gtod_ctx* c) {
-  void* base = nullptr;
-  const hipError_t e = scratch_address(c->device, &base);
+  DeviceStatics d;
+  const hipError_t e = device_statics(c->device, &d);
   if (e != hipSuccess)
     return fail(c, GTOD_EDEVICE,
-                std::string("hipGetSymbolAddress(scratch): ") + hipGetErrorString(e));
+                std::string("device scratch and tables: ") + hipGetErrorString(e));
+  void* const base = d.scratch;
+  c->pink_table = d.pink_table;
   StreamWs& w = c->na;
   w.d_stage = static_cast<char*>(base);
   w.panel = reinterpret_cast<float*>(static_cast<char*>(base) + kSlots * kSlotBytes);
@@ -986,12 +1003,10 @@ static gtod_status simulate(gtod_ctx* c, const gtod_job* jobs, int32_t n_jobs,
       a.t_total = j.t_total;
       a.out_ld = j.out_ld ? j.out_ld : j.t_total;
       a.accumulate = acc;
-      a.tab = w->pink;
-      a.tab_w = w->pink;
+      a.tab = c->pink_table;
       a.scratch = w->pink + kPinkTableFloat2;
       const int64_t S = (int64_t)j.n_pix * f.K;
       const int64_t per = plan[i].pink_per;
-      launch_pink_tables(a, s);
       for (int64_t s0 = 0; s0 < S; s0 += per) {
         a.s0 = s0;
         a.n_series = (int)std::min<int64_t>(per, S - s0);

@@ -159,10 +159,10 @@ __global__ __launch_bounds__(64) void k_beam_panels(BeamArgs a) {
 // One thread per grid node and kEvalF frequencies.
 constexpr int kEvalF = 8;
 __global__ __launch_bounds__(256) void k_beam_eval(BeamArgs a) {
-  const int per = a.n_a * a.n_b;
-  const int id = blockIdx.x * 256 + threadIdx.x;
+  const int64_t per = (int64_t)a.n_a * a.n_b;
+  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (id >= per) return;
-  const int ib = id / a.n_a, ia = id % a.n_a;
+  const int ib = (int)(id / a.n_a), ia = (int)(id % a.n_a);
   const double rho = sqrt((ia * a.da) * (ia * a.da) + (ib * a.db) * (ib * a.db));
   const double k = 2.0 * kPi * rho / kC * a.r_tel;
   const int f1 = min((int)(blockIdx.y + 1) * kEvalF, a.F);
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(256) void k_beam_eval(BeamArgs a) {
     double q = c[kBeamTerms - 1];
 #pragma unroll
     for (int m = kBeamTerms - 2; m >= 0; --m) q = fma(q, t, c[m]);
-    a.table[(int64_t)f * per + id] = (float)(q * q);
+    a.table[f * per + id] = (float)(q * q);
   }
 }
 
@@ -426,13 +426,13 @@ void launch_beam_polynomials(const BeamArgs& a, hipStream_t s) {
 }
 
 void launch_beam_eval(const BeamArgs& a, hipStream_t s) {
-  const int per = a.n_a * a.n_b;
+  const int64_t per = (int64_t)a.n_a * a.n_b;
   for (int f0 = 0; f0 < a.F; f0 += 65535 * kEvalF) {
     BeamArgs b = a;
     b.F = std::min(a.F - f0, 65535 * kEvalF);
     b.nu += f0;
-    b.table += (int64_t)f0 * per;
-    hipLaunchKernelGGL(k_beam_eval, dim3((per + 255) / 256, (b.F + kEvalF - 1) / kEvalF),
+    b.table += f0 * per;
+    hipLaunchKernelGGL(k_beam_eval, dim3((unsigned)((per + 255) / 256), (b.F + kEvalF - 1) / kEvalF),
                        dim3(256), 0, s, b);
   }
 }

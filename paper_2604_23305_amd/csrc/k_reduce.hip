@@ -68,22 +68,19 @@ __device__ inline int map_cell(const ReduceArgs& a, double x, double y) {
 
 }  // namespace
 
+// Scan offsets, and the cosecants of spaxel blockIdx.y where they are kept.
 __global__ __launch_bounds__(kRdThreads) void k_rd_scan(ReduceArgs a) {
   const int64_t t = (int64_t)blockIdx.x * kRdThreads + threadIdx.x;
   if (t >= a.T) return;
+  const int p = blockIdx.y;
   double phi, th;
   scan_offsets(a.scan_kind, a.r_petal, a.omega, a.Omega, a.traj, a.t0 + t,
                a.f_s, &phi, &th);
-  a.scan_phi[t] = phi;
-  a.scan_th[t] = th;
-}
-
-// Cosecants of spaxel blockIdx.y.
-__global__ __launch_bounds__(kRdThreads) void k_rd_csc(ReduceArgs a) {
-  const int64_t t = (int64_t)blockIdx.x * kRdThreads + threadIdx.x;
-  if (t >= a.T) return;
-  const int p = blockIdx.y;
-  const double th = a.scan_th[t];
+  if (p == 0) {
+    a.scan_phi[t] = phi;
+    a.scan_th[t] = th;
+  }
+  if (!a.csc_common) return;
   a.csc_common[p * a.T + t] = 1.0 / sin((th + a.theta0) + a.dtheta[p]);
   if (a.csc_grid) a.csc_grid[p * a.T + t] = 1.0 / sin(th + (a.theta0 + a.dtheta[p]));
 }
@@ -576,11 +573,9 @@ __global__ __launch_bounds__(kRdThreads) void k_rd_combine(ReduceArgs a) {
 }
 
 void launch_reduce_setup(const ReduceArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_rd_scan, dim3((unsigned)((a.T + kRdThreads - 1) / kRdThreads)),
+  hipLaunchKernelGGL(k_rd_scan,
+                     dim3((unsigned)((a.T + kRdThreads - 1) / kRdThreads), a.csc_common ? a.P : 1),
                      dim3(kRdThreads), 0, s, a);
-  if (a.csc_common)
-    hipLaunchKernelGGL(k_rd_csc, dim3((unsigned)((a.T + kRdThreads - 1) / kRdThreads), a.P),
-                       dim3(kRdThreads), 0, s, a);
   if (a.pwv_part && a.pwv)
     hipLaunchKernelGGL(k_rd_pwv_parts, dim3(4), dim3(kPwvThreads), 0, s, a);
   else

@@ -164,8 +164,9 @@ __device__ __forceinline__ void contraction_epilogue(
         pkd[q] = e[2 * q].c0 + (double)sn[2 * q * kEpiPitch] * e[2 * q].u0;
         pk[q] = (float)pkd[q];
         const double n2 = e[2 * q].c1 + (double)sn[(32 + 2 * q) * kEpiPitch] * e[2 * q].u1;
-        // sigma to FP32 rounding (its tolerance is 1e-5)
-        sg[q] = sqrtf((float)(fmax(n2, 0.0) * (double)a.fs_half));
+        // sigma to FP32 rounding (its tolerance is 1e-5); its square times
+        // 2^40, as that of a faint channel is below the normal range
+        sg[q] = 0x1p-20f * sqrtf((float)(fmax(n2, 0.0) * ((double)a.fs_half * 0x1p40)));
         v[q] = 0.f;
       }
       if (a.photon) {

@@ -77,6 +77,7 @@ struct GemmArgs {
   const float* B;        // [3][Kp][Fp] B0, B1', B2 (fp32)
   const uint16_t* Tb;    // BF16 halves of the responses, tiled
   const uint16_t* Th;    // FP16 halves, tiled, each channel scaled
+  const float* unscale;  // [Fp] 2^-d_j
   const double* unit0;   // [Kp] worth of an FP16-path C0 unit (W)
   const double* unit1;   // [Kp] worth of an FP16-path C1 unit (W^2/Hz)
   const double* c0;      // [Kp] reference P_KID
@@ -85,11 +86,11 @@ struct GemmArgs {
   int p0, n_pix, Tc, Tpad;
   int64_t t0, out_t0, out_ld;
   float fs_half;
-  // The panel carries bin j's spectral power times 2^(pexp + d_j) and the
-  // responses 2^-d_j (2^-2 d_j for B2), powers of two chosen so that every
-  // bin's reference power lies in [2, 4): the products carry 2^pexp, which
-  // keeps them in the normal FP32 range, and the epilogue multiplies by
-  // pinv = 2^-pexp.
+  // Split jobs: the panel carries the spectral powers times 2^pexp, which
+  // brings the largest reference power to [2, 4) and keeps the products in the
+  // normal FP32 range; the epilogue multiplies by pinv = 2^-pexp.  FP32 jobs:
+  // bin j's power times 2^(pexp + d_j), which brings every bin's reference
+  // power to [2, 4), and the FP16 responses 2^-d_j (2^-2 d_j for B2).
   double pinv;
   float pinv_f;
   uint32_t key0, key1;
@@ -310,18 +311,24 @@ int launch_reduce_grid(const ReduceArgs& a, hipStream_t s);  // 0 ok
 void launch_reduce_combine(const ReduceArgs& a, hipStream_t s);
 void launch_spec_setup(const SpecSetupArgs& a, const PassTable& pt,
                        hipStream_t s);
-// E, D, W, Pref times sx[j] and the responses times sb[j] (B2: twice).
-void launch_scale_bins(float* E, float* D, float* W, float* Pref, float* B, int Kp, int Fp,
-                       const float* sx, const float* sb, hipStream_t s);
+// Power-of-two scales of a setup's spectra for the two contractions.
+struct SpecScaleArgs {
+  int Fp, pexp;
+  float* E; float* D; float* W; float* Pref;   // [Fp] each, scaled in place
+  float* H;                                    // [4][Fp] scaled bin by bin
+  int* d;                                      // [Fp]
+  float* unscale;                              // [Fp] 2^-d
+};
+void launch_scale_spectra(const SpecScaleArgs& a, hipStream_t s);
 void launch_panel(const PanelArgs& a, hipStream_t s);
 void launch_gemm_f32(const GemmArgs& a, hipStream_t s);
 void launch_gemm_bf16(const GemmArgs& a, hipStream_t s);
 // Bytes of the tiled halves of a Kp x Fp setup's responses, and the kernels
 // that build them (with the FP16 halves' channel scales e0, e1, unit0,
-// unit1) from the FP32 responses.
+// unit1) from the FP32 responses and the bins' scales d.
 size_t tiled_response_bytes(int Kp, int Fp, bool f16);
-void launch_tile_responses(const float* B, int* e0, int* e1, double* unit0, double* unit1,
-                           uint16_t* Tb, uint16_t* Th, int Kp, int Fp, int pexp,
+void launch_tile_responses(const float* B, const int* d, int* e0, int* e1, double* unit0,
+                           double* unit1, uint16_t* Tb, uint16_t* Th, int Kp, int Fp, int pexp,
                            hipStream_t s);
 void launch_pink_tables(float2* tab, hipStream_t s);
 void launch_pink_pass1(const PinkArgs& a, hipStream_t s);

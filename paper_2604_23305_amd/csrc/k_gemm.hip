@@ -10,14 +10,17 @@
 // h = f16(v) and l = f16(v - h) (round to nearest even): 22 bits, and three
 // products (l h, h l, h h) for each of x B0, x B1' and x^2 B2.  The panel
 // holds x scaled per bin so that the reference power of every bin lies in
-// [2, 4) and each response channel is scaled to a maximum in [2^13, 2^14),
-// all by powers of two that cancel or are undone in the epilogue.  The
-// absolute error of the halves of x, at most 2^-25, then is 2^-26 of the
-// bin's power, below the FP32 rounding of the panel itself.  Rows beyond
+// [2, 4) (down to 2^-123 W/Hz; a fainter bin's is scaled by 2^124), and each
+// response channel is scaled to a maximum in [2^13, 2^14), all by powers of two
+// that cancel or are undone in the epilogue.  The halves of x are off by at
+// most max(2^-25, 2^-23 |x|): near the reference (|x| < 1/2) that is 2^-26 of
+// the bin's power, below the FP32 rounding of the panel itself, far from it up
+// to twice the FP32 rounding of x.  Rows beyond
 // the FP16 range (|x| > 255, i.e. a deviation of 64 to 128 times the
 // reference power, and infinities or NaN) make an accumulator non-finite;
-// the wave then recomputes its tile with FP32 MFMAs on the FP32 operands
-// and stores such rows from there, so the choice depends on the row alone.
+// the wave then recomputes its tile with FP32 MFMAs on FP32 operands (x with
+// its bin's scale taken out again, and the unscaled responses) and stores such
+// rows from there, so the choice depends on the row alone.
 // Why: the FP32 matrix rate is 1/16 of the 16-bit one and nine 16-bit
 // products replace three FP32 ones.
 //
@@ -205,35 +208,36 @@ size_t tiled_response_bytes(int Kp, int Fp, bool f16) {
   return groups * (size_t)(Fp / KC) * (f16 ? 6 : 5) * kPlaneBytes;
 }
 
-// Power-of-two scale of channel k's FP16 responses: the largest |B0| and
-// the largest of |B1'|, |B2| 2^-p come to [2^13, 2^14).  unit0, unit1 are
+// Power-of-two scale of channel k's FP16 responses: the largest |B0| 2^-d and
+// the largest of |B1'| 2^-d, |B2| 2^(-2 d - p) come to [2^13, 2^14).  unit0, unit1 are
 // what one accumulator unit is worth; a channel without response, or with
 // a non-finite one, is left unscaled.
-__global__ __launch_bounds__(256) void k_response_units(const float* __restrict__ B, int Kp,
+__global__ __launch_bounds__(256) void k_response_units(const float* __restrict__ B,
+                                                        const int* __restrict__ d, int Kp,
                                                         int Fp, int pexp, int* e0, int* e1,
                                                         double* unit0, double* unit1) {
-  __shared__ float m0[256], m1[256];
+  __shared__ double m0[256], m1[256];
   const int k = blockIdx.x;
   const int64_t KF = (int64_t)Kp * Fp;
   const float* b = B + (int64_t)k * Fp;
-  const float s2 = ldexpf(1.0f, -pexp);
-  float x0 = 0.f, x1 = 0.f;
+  double x0 = 0.0, x1 = 0.0;
   for (int j = threadIdx.x; j < Fp; j += 256) {
-    x0 = fmaxf(x0, fabsf(b[j]));
-    x1 = fmaxf(x1, fmaxf(fabsf(b[KF + j]), fabsf(b[2 * KF + j] * s2)));
+    x0 = fmax(x0, ldexp(fabs((double)b[j]), -d[j]));
+    x1 = fmax(x1, fmax(ldexp(fabs((double)b[KF + j]), -d[j]),
+                       ldexp(fabs((double)b[2 * KF + j]), -2 * d[j] - pexp)));
   }
   m0[threadIdx.x] = x0;
   m1[threadIdx.x] = x1;
   __syncthreads();
   for (int st = 128; st > 0; st >>= 1) {
     if ((int)threadIdx.x < st) {
-      m0[threadIdx.x] = fmaxf(m0[threadIdx.x], m0[threadIdx.x + st]);
-      m1[threadIdx.x] = fmaxf(m1[threadIdx.x], m1[threadIdx.x + st]);
+      m0[threadIdx.x] = fmax(m0[threadIdx.x], m0[threadIdx.x + st]);
+      m1[threadIdx.x] = fmax(m1[threadIdx.x], m1[threadIdx.x + st]);
     }
     __syncthreads();
   }
   if (threadIdx.x != 0) return;
-  auto exponent = [](float m) { return (m > 0.f && isfinite(m)) ? 13 - ilogbf(m) : 0; };
+  auto exponent = [](double m) { return (m > 0.0 && isfinite(m)) ? 13 - ilogb(m) : 0; };
   e0[k] = exponent(m0[0]);
   e1[k] = exponent(m1[0]);
   unit0[k] = ldexp(1.0, -pexp - e0[k]);
@@ -245,11 +249,13 @@ __global__ __launch_bounds__(256) void k_response_units(const float* __restrict_
 // i.e. the LDS image of the stage, contiguous:
 // T[g][s][m][r][slot] = B_m[64 g + r][16 s + 8 (slot ^ swb(r)) .. + 7],
 // zero for channels past the padded matrix.  The B2 planes are taken times
-// 2^-p, so that x^2 B2 adds straight into C1.
+// 2^-p, so that x^2 B2 adds straight into C1; the FP16 halves' scales (the
+// channel's, the bin's) go into the same exponent, so that none of them
+// underflows by itself.
 template <bool F16>
-__global__ void k_tile_responses(const float* __restrict__ B, const int* __restrict__ e0,
-                                 const int* __restrict__ e1, uint16_t* __restrict__ T,
-                                 int Kp, int Fp, int pexp, int64_t n_slots) {
+__global__ void k_tile_responses(const float* __restrict__ B, const int* __restrict__ d,
+                                 const int* __restrict__ e0, const int* __restrict__ e1, 
+                                 uint16_t* __restrict__ T, int Kp, int Fp, int pexp, int64_t n_slots) {
   constexpr int NPL = Half<F16>::kPlanes;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_slots) return;
@@ -265,11 +271,12 @@ __global__ void k_tile_responses(const float* __restrict__ B, const int* __restr
   const bool low = !(m & 1) && (F16 || m < 4);
   uint16_t v[8] = {};
   if (ch < Kp) {
-    const float* src = B + ((int64_t)mat * Kp + ch) * Fp + s * KC + 8 * (slot ^ swb(r));
+    const int j = s * KC + 8 * (slot ^ swb(r));
+    const float* src = B + ((int64_t)mat * Kp + ch) * Fp + j;
     const int e = (F16 ? (mat == 0 ? e0[ch] : e1[ch]) : 0) - (mat == 2 ? pexp : 0);
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      const float x = ldexpf(src[k], e);
+      const float x = ldexpf(src[k], F16 ? e - (mat == 2 ? 2 : 1) * d[j + k] : e);
       if constexpr (F16) {
         const _Float16 h = (_Float16)x;
         const _Float16 o = low ? (_Float16)(x - (float)h) : h;
@@ -289,17 +296,17 @@ __global__ void k_tile_responses(const float* __restrict__ B, const int* __restr
   reinterpret_cast<uint4*>(T)[i] = w;
 }
 
-void launch_tile_responses(const float* B, int* e0, int* e1, double* unit0, double* unit1,
-                           uint16_t* Tb, uint16_t* Th, int Kp, int Fp, int pexp,
+void launch_tile_responses(const float* B, const int* d, int* e0, int* e1, double* unit0,
+                           double* unit1, uint16_t* Tb, uint16_t* Th, int Kp, int Fp, int pexp,
                            hipStream_t s) {
-  hipLaunchKernelGGL(k_response_units, dim3(Kp), dim3(256), 0, s, B, Kp, Fp, pexp, e0, e1,
-                     unit0, unit1);
+  hipLaunchKernelGGL(k_response_units, dim3(Kp), dim3(256), 0, s, B, d, Kp, Fp, pexp, e0,
+                     e1, unit0, unit1);
   const int64_t nb = (int64_t)(tiled_response_bytes(Kp, Fp, false) / 16);
   const int64_t nh = (int64_t)(tiled_response_bytes(Kp, Fp, true) / 16);
   hipLaunchKernelGGL(k_tile_responses<false>, dim3((unsigned)((nb + 255) / 256)), dim3(256),
-                     0, s, B, e0, e1, Tb, Kp, Fp, pexp, nb);
+                     0, s, B, d, e0, e1, Tb, Kp, Fp, pexp, nb);
   hipLaunchKernelGGL(k_tile_responses<true>, dim3((unsigned)((nh + 255) / 256)), dim3(256),
-                     0, s, B, e0, e1, Th, Kp, Fp, pexp, nh);
+                     0, s, B, d, e0, e1, Th, Kp, Fp, pexp, nh);
 }
 
 // ---------------------------------------------------------------------------
@@ -635,7 +642,11 @@ __global__ __launch_bounds__(64 * WR * WC * SPL, 1) void k_contract(GemmArgs a) 
     for (int k0 = 0; k0 < a.Fp; k0 += 8) {
       float4 x[NJ], v[NI][3];
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) x[j] = *reinterpret_cast<const float4*>(xr[j] + k0);
+      for (int j = 0; j < NJ; ++j) {
+        x[j] = *reinterpret_cast<const float4*>(xr[j] + k0);
+        const float4 u = *reinterpret_cast<const float4*>(a.unscale + 4 * h + k0);
+        for (int e = 0; e < 4; ++e) x[j][e] *= u[e];
+      }
 #pragma unroll
       for (int i = 0; i < NI; ++i)
 #pragma unroll

@@ -186,32 +186,37 @@ __global__ __launch_bounds__(256) void k_reference(SpecSetupArgs a) {
   }
 }
 
-// One block per padded channel for its responses, the last one for the
-// spectra.
-__global__ __launch_bounds__(256) void k_scale_bins(float* E, float* D, float* W, float* Pref,
-                                                    float* B, int Kp, int Fp,
-                                                    const float* sx, const float* sb) {
-  const int k = blockIdx.x;
-  const int64_t KF = (int64_t)Kp * Fp;
-  for (int j = threadIdx.x; j < Fp; j += 256) {
-    if (k == Kp) {
-      E[j] *= sx[j];
-      D[j] *= sx[j];
-      W[j] *= sx[j];
-      Pref[j] *= sx[j];
-    } else {
-      float* b = B + (int64_t)k * Fp + j;
-      b[0] *= sb[j];
-      b[KF] *= sb[j];
-      b[2 * KF] *= sb[j] * sb[j];
-    }
+// The spectra times 2^pexp in place, and times 2^(pexp + d_j) in H (E, D, W,
+// Pref).  d_j brings the reference power of bin j to [2, 4) as long as nothing
+// of the bin then exceeds 2^125.  A bin without reference power takes the
+// largest scale: any power that FP32 resolves there lies beyond the FP16 range
+// of the contraction, which then takes the row with FP32 operands.
+__global__ void k_scale_spectra(SpecScaleArgs a) {
+  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  if (j >= a.Fp) return;
+  float* const v[4] = {a.E + j, a.D + j, a.W + j, a.Pref + j};
+  double most = 0.0;
+  bool finite = true;
+  for (int q = 0; q < 4; ++q) {
+    most = fmax(most, fabs((double)*v[q]));
+    finite &= isfinite(*v[q]);
+  }
+  int d = 0;
+  if (finite && most > 0.0) {
+    const double ref = fabs((double)*v[3]);
+    const int top = max(0, min(124, 124 - ilogb(most)) - a.pexp);
+    d = ref > 0.0 ? max(0, min(1 - ilogb(ref) - a.pexp, top)) : top;
+  }
+  a.d[j] = d;
+  a.unscale[j] = ldexpf(1.0f, -d);
+  for (int q = 0; q < 4; ++q) {
+    a.H[q * a.Fp + j] = ldexpf(*v[q], a.pexp + d);
+    *v[q] = ldexpf(*v[q], a.pexp);
   }
 }
 
-void launch_scale_bins(float* E, float* D, float* W, float* Pref, float* B, int Kp, int Fp,
-                       const float* sx, const float* sb, hipStream_t s) {
-  hipLaunchKernelGGL(k_scale_bins, dim3(Kp + 1), dim3(256), 0, s, E, D, W, Pref, B, Kp, Fp,
-                     sx, sb);
+void launch_scale_spectra(const SpecScaleArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(k_scale_spectra, dim3((a.Fp + 127) / 128), dim3(128), 0, s, a);
 }
 
 void launch_spec_setup(const SpecSetupArgs& a, const PassTable& pt,

@@ -36,6 +36,8 @@ struct SpecObj {
   float* D = nullptr;
   float* W = nullptr;
   float* Pref = nullptr;
+  float* H = nullptr;       // E, D, W, Pref as FP32 jobs take them
+  float* unscale = nullptr;
   float* B = nullptr;
   uint16_t* Tb = nullptr;   // BF16 halves of the responses, tiled
   uint16_t* Th = nullptr;   // FP16 halves, tiled, each channel scaled
@@ -43,7 +45,7 @@ struct SpecObj {
   double* unit1 = nullptr;
   double* c0 = nullptr;
   double* c1 = nullptr;
-  int pexp = 0;   // the contraction's products carry 2^pexp
+  int pexp = 0;   // the spectra carry 2^pexp
   std::vector<double> nep2ref;
   // FP64 tables kept for the skydip, and its brightness-temperature scale
   double t_atm = 0;
@@ -739,6 +741,8 @@ gtod_status gtod_load_filters(gtod_ctx* c, const gtod_spectral_desc* d, int32_t*
   res((void**)&so.D, Fp * 4);
   res((void**)&so.W, Fp * 4);
   res((void**)&so.Pref, Fp * 4);
+  res((void**)&so.H, 4 * Fp * 4);
+  res((void**)&so.unscale, Fp * 4);
   res((void**)&so.B, 3 * Kp * Fp * 4);
   res((void**)&so.Tb, tiled_response_bytes((int)Kp, (int)Fp, false));
   res((void**)&so.Th, tiled_response_bytes((int)Kp, (int)Fp, true));
@@ -759,8 +763,7 @@ gtod_status gtod_load_filters(gtod_ctx* c, const gtod_spectral_desc* d, int32_t*
   };
   double *d_nu, *d_w, *d_eta, *d_pool, *d_prm, *d_T, *d_f = nullptr, *d_R = nullptr,
          *d_pk = nullptr, *d_mat = nullptr, *d_pref64, *d_B64;
-  int *d_type, *d_coup, *d_off, *d_order, *d_e;
-  float* d_scale;
+  int *d_type, *d_coup, *d_off, *d_order, *d_e, *d_bin;
   tmpa((void**)&d_nu, F * 8);
   tmpa((void**)&d_w, F * 8);
   tmpa((void**)&d_eta, (size_t)d->n_pwv * F * 8);
@@ -772,7 +775,7 @@ gtod_status gtod_load_filters(gtod_ctx* c, const gtod_spectral_desc* d, int32_t*
   tmpa((void**)&d_off, std::max<size_t>(poff.size(), 1) * 4);
   tmpa((void**)&d_order, K * 4);
   tmpa((void**)&d_e, 2 * Kp * 4);
-  tmpa((void**)&d_scale, 2 * Fp * 4);
+  tmpa((void**)&d_bin, Fp * 4);
   tmpa((void**)&d_pref64, Fp * 8);
   tmpa((void**)&d_B64, (size_t)2 * F * K * 8);
   if (d->filter_mode == GTOD_FILT_MATRIX) {
@@ -863,27 +866,17 @@ gtod_status gtod_load_filters(gtod_ctx* c, const gtod_spectral_desc* d, int32_t*
     e = hipMemcpy(so.nep2ref.data(), so.c1, K * 8, hipMemcpyDeviceToHost);
   }
   if (e == hipSuccess) {
-    // power-of-two scales bringing every bin's reference power to [2, 4)
-    // (a bin below 2^-20 of the largest is scaled as one at 2^-20)
+    // power-of-two scale bringing the largest reference power to [2, 4)
     std::vector<double> pref(Fp);
     e = hipMemcpy(pref.data(), d_pref64, Fp * 8, hipMemcpyDeviceToHost);
     double mx = 0.0;
     for (double v : pref) mx = std::max(mx, std::fabs(v));
     so.pexp = (mx > 0.0 && std::isfinite(mx)) ? 1 - std::ilogb(mx) : 0;
     so.pexp = std::max(-60, std::min(so.pexp, 100));
-    std::vector<float> sc(2 * Fp);
-    for (int64_t j = 0; j < Fp; ++j) {
-      const double v = std::fabs(pref[j]);
-      const int d = (v > 0.0 && std::isfinite(v))
-          ? std::max(0, std::min(1 - std::ilogb(v) - so.pexp, 20)) : 0;
-      sc[j] = std::ldexp(1.0f, so.pexp + d);
-      sc[Fp + j] = std::ldexp(1.0f, -d);
-    }
-    cp(d_scale, sc.data(), 2 * Fp * 4);
     if (e == hipSuccess) {
-      launch_scale_bins(so.E, so.D, so.W, so.Pref, so.B, so.Kp, so.Fp, d_scale, d_scale + Fp,
-                        nullptr);
-      launch_tile_responses(so.B, d_e, d_e + Kp, so.unit0, so.unit1, so.Tb, so.Th, so.Kp,
+      launch_scale_spectra(SpecScaleArgs{so.Fp, so.pexp, so.E, so.D, so.W, so.Pref, so.H, d_bin,
+                                         so.unscale}, nullptr);
+      launch_tile_responses(so.B, d_bin, d_e, d_e + Kp, so.unit0, so.unit1, so.Tb, so.Th, so.Kp,
                             so.Fp, so.pexp, nullptr);
       e = hipGetLastError();
       if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -1025,10 +1018,11 @@ static gtod_status simulate(gtod_ctx* c, const gtod_job* jobs, int32_t n_jobs,
     const int64_t rows_cap = plan[i].rows_cap, Tc_max = plan[i].Tc_max;
     PanelArgs pa{};
     pa.tau = f.tau;
-    pa.E = f.E;
-    pa.D = f.D;
-    pa.W = f.W;
-    pa.Pref = f.Pref;
+    const bool split = plan[i].precision == GTOD_PREC_SPLIT_BF16;
+    pa.E = split ? f.E : f.H;
+    pa.D = split ? f.D : f.H + f.Fp;
+    pa.W = split ? f.W : f.H + 2 * f.Fp;
+    pa.Pref = split ? f.Pref : f.H + 3 * f.Fp;
     pa.F = f.F;
     pa.Fp = f.Fp;
     pa.n_pwv = f.n_pwv;
@@ -1084,6 +1078,7 @@ static gtod_status simulate(gtod_ctx* c, const gtod_job* jobs, int32_t n_jobs,
     ga.B = f.B;
     ga.Tb = f.Tb;
     ga.Th = f.Th;
+    ga.unscale = f.unscale;
     ga.unit0 = f.unit0;
     ga.unit1 = f.unit1;
     ga.c0 = f.c0;
@@ -1126,7 +1121,7 @@ static gtod_status simulate(gtod_ctx* c, const gtod_job* jobs, int32_t n_jobs,
         ga.t0 = tb;
         ga.Tc = Tc;
         ga.Tpad = Tpad;
-        if (plan[i].precision == GTOD_PREC_SPLIT_BF16)
+        if (split)
           timed(c, GTOD_KERNEL_GEMM_BF16, flop, s, [&] { launch_gemm_bf16(ga, s); });
         else
           timed(c, GTOD_KERNEL_GEMM_F32, flop, s, [&] { launch_gemm_f32(ga, s); });

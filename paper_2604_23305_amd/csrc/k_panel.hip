@@ -205,18 +205,25 @@ struct Bins {
 };
 
 // dP of a row: t0, t1 the table rows around its PWV, ps the source power.
+// csc is the same in the whole workgroup: a row at an elevation without airmass
+// (csc < 0), which only a user trajectory reaches, takes the library's expm1f,
+// which overflows to the infinity it should.
 __device__ __forceinline__ f32x4 row_deviation(const Bins& b, f32x4 t0, f32x4 t1, f32x4 ps,
                                                float lw, float csc, bool src, uint32_t* far) {
   f32x4 dP;
+  auto bins = [&](auto opacity) {
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const float tz = (1.f - lw) * t0[k] + lw * t1[k];
-    const float xi = one_minus_exp(csc * tz);
-    float P = b.E[k] + xi * b.D[k];
-    if (src) P += (1.f - xi) * (b.W[k] * ps[k]);
-    dP[k] = P - b.Pr[k];
-    *far += (uint32_t)__builtin_popcountll(__ballot(fabsf(dP[k]) > 0.125f * P));
-  }
+    for (int k = 0; k < 4; ++k) {
+      const float tz = (1.f - lw) * t0[k] + lw * t1[k];
+      const float xi = opacity(csc * tz);
+      float P = b.E[k] + xi * b.D[k];
+      if (src) P += (1.f - xi) * (b.W[k] * ps[k]);
+      dP[k] = P - b.Pr[k];
+      *far += (uint32_t)__builtin_popcountll(__ballot(fabsf(dP[k]) > 0.125f * P));
+    }
+  };
+  if (csc >= 0.f) bins([](float x) { return one_minus_exp(x); });
+  else bins([](float x) { return -expm1f(-x); });
   return dP;
 }
 

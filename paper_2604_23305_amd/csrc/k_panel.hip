@@ -206,12 +206,14 @@ struct Bins {
 
 // dP of a row: t0, t1 the table rows around its PWV, ps the source power.
 // csc is the same in the whole workgroup: a row at an elevation without airmass
-// (csc < 0), which only a user trajectory reaches, takes the library's expm1f,
-// which overflows to the infinity it should.
-__device__ __forceinline__ f32x4 row_deviation(const Bins& b, f32x4 t0, f32x4 t1, f32x4 ps,
-                                               float lw, float csc, bool src, uint32_t* far) {
+// (csc negative or infinite), which only a user trajectory reaches, takes the
+// library's expm1f, which overflows to the infinity it should, and leaves the
+// bins of the padding, where 0 times infinity would be NaN, at zero.
+__device__ __forceinline__ f32x4 row_deviation(const Bins& b, int F, f32x4 t0, f32x4 t1,
+                                               f32x4 ps, float lw, float csc, bool src,
+                                               uint32_t* far) {
   f32x4 dP;
-  auto bins = [&](auto opacity) {
+  auto bins = [&](auto opacity, auto padded) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const float tz = (1.f - lw) * t0[k] + lw * t1[k];
@@ -219,11 +221,14 @@ __device__ __forceinline__ f32x4 row_deviation(const Bins& b, f32x4 t0, f32x4 t1
       float P = b.E[k] + xi * b.D[k];
       if (src) P += (1.f - xi) * (b.W[k] * ps[k]);
       dP[k] = P - b.Pr[k];
+      if (padded(b.j + k)) dP[k] = P = 0.f;
       *far += (uint32_t)__builtin_popcountll(__ballot(fabsf(dP[k]) > 0.125f * P));
     }
   };
-  if (csc >= 0.f) bins([](float x) { return one_minus_exp(x); });
-  else bins([](float x) { return -expm1f(-x); });
+  if (csc >= 0.f && csc < INFINITY)
+    bins([](float x) { return one_minus_exp(x); }, [](uint32_t) { return false; });
+  else
+    bins([](float x) { return -expm1f(-x); }, [&](uint32_t j) { return j >= (uint32_t)F; });
   return dP;
 }
 
@@ -277,7 +282,7 @@ __device__ __forceinline__ void panel_rows(const PanelArgs& a, int n_rows, int f
         }
         f32x4 dP = {0.f, 0.f, 0.f, 0.f};
         if (q[u].valid)
-          dP = row_deviation(b, t0[u], t1[u], ps, q[u].lw, q[u].csc, src, &far);
+          dP = row_deviation(b, a.F, t0[u], t1[u], ps, q[u].lw, q[u].csc, src, &far);
         // past the caches: the panel is larger than them, and what it would
         // push out (table rows, cube corners) is read again
         if (in) __builtin_nontemporal_store(dP, reinterpret_cast<f32x4*>(out[u] + b.j));

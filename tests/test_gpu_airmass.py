@@ -58,3 +58,24 @@ def test_below_the_horizon(F, prec):
     assert lost.any() and not np.isfinite(got[lost]).any()
     up = np.sin(el) > 0
     assert (np.abs(got - ref)[:, up] <= 1e-6 * ref[:, up]).all()
+
+
+@pytest.mark.parametrize("F", [33, 40, 64])
+@pytest.mark.parametrize("prec", [g.PREC_FP32, g.PREC_SPLIT_BF16])
+def test_on_the_horizon(F, prec):
+    """Elevation 0 exactly: the airmass is infinite and every bin opaque.  The
+    padding of the frequency axis, which has no optical depth, adds nothing.
+    Single bins, off by a few roundings of the operands: 2^-20, 16-bit ones
+    2^-13."""
+    sc = scenario(F, np.array([T0, 0.0, T0]))
+    c = new_ctx()
+    try:
+        _, out = run_signal(c, sc, precision=prec, photon_noise=False)
+        got = out.p_kid.cpu().numpy()[0].astype(np.float64)
+    finally:
+        g.free(c)
+    with np.errstate(all="ignore"):
+        ref = oracle.tod.simulate(sc, photon_noise=False)["p_kid"][0]
+    assert np.isfinite(ref).all()
+    tol = 2.0 ** (-20 if prec == g.PREC_FP32 else -13)
+    assert (np.abs(got - ref) <= tol * ref).all()

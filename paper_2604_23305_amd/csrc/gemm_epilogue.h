@@ -70,11 +70,11 @@ struct EpiUnits {
   double same;
 };
 
-// store[j]: whether this lane's row of row tile j is written.
+// store[i][j]: whether this lane's row of tile (i, j) is written.
 template <int NI, int NJ>
 __device__ __forceinline__ void contraction_epilogue(
     const GemmArgs& a, f32x16 (&acc)[2][NI][NJ], char* lds,
-    int64_t row_base, int ch_base, int n_live, const bool (&store)[NJ],
+    int64_t row_base, int ch_base, int n_live, const bool (&store)[NI][NJ],
     const EpiUnits& units) {
   constexpr int NU = epi_unit(NI), kUnits = NI / NU;   // channel tiles per unit, units per row tile
   const int lane = threadIdx.x & 63;
@@ -124,7 +124,8 @@ __device__ __forceinline__ void contraction_epilogue(
     if (u + 1 < NJ * kUnits) fetch_prev(u + 1);
     if (n <= 0) continue;
     const int pl = pixel(j), tl = sample(j);
-    const bool valid = store[j] && pl < a.n_pix && tl < a.Tc;
+    const bool store0 = store[i0][j], store1 = store[i0 + NU - 1][j];
+    const bool valid = (store0 || store1) && pl < a.n_pix && tl < a.Tc;
     const uint32_t t = (uint32_t)(a.t0 + tl), p = (uint32_t)(a.pix0 + a.p0 + pl);
     const PhiloxRow pr(t, p, a.key0, a.key1);
     __builtin_amdgcn_wave_barrier();
@@ -154,6 +155,7 @@ __device__ __forceinline__ void contraction_epilogue(
     const float* const pv = reinterpret_cast<const float*>(
         prev + (u & 1) * (NU * kEpiPrevBytes)) + lane;
     for (int q0 = 0; 2 * q0 < n; q0 += kU) {
+      if (!(q0 < 16 ? store0 : store1)) continue;
       const EpiChannel* const e = kh + 2 * q0;
       const float* const sn = th + (q0 >> 4) * (kEpiTileBytes / 4) + (q0 & 15) * 2 * kEpiPitch;
       double pkd[kU];

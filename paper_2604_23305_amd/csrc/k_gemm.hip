@@ -17,10 +17,12 @@
 // the bin's power, below the FP32 rounding of the panel itself, far from it up
 // to twice the FP32 rounding of x.  Rows beyond
 // the FP16 range (|x| > 255, i.e. a deviation of 64 to 128 times the
-// reference power, and infinities or NaN) make an accumulator non-finite;
-// the wave then recomputes its tile with FP32 MFMAs on FP32 operands (x with
-// its bin's scale taken out again, and the unscaled responses) and stores such
-// rows from there, so the choice depends on the row alone.
+// reference power, and infinities or NaN) make their accumulators non-finite,
+// and so does a response that is not finite itself; the wave then recomputes
+// its tile with FP32 MFMAs on FP32 operands (x with its bin's scale taken out
+// again, and the unscaled responses) and stores the rows of 32 channels with
+// such an accumulator from there.  32 channels are a tile in every shape, so
+// the choice depends on the row and the setup alone.
 // Why: the FP32 matrix rate is 1/16 of the 16-bit one and nine 16-bit
 // products replace three FP32 ones.
 //
@@ -595,29 +597,31 @@ __global__ __launch_bounds__(64 * WR * WC * SPL, 1) void k_contract(GemmArgs a) 
   if (n_live == 0) return;
   char* const spk = ring + wave * epi_wave_bytes(NI);
   const int64_t row_w = row0 + rw * 32 * NJ;
-  bool store[NJ];
+  bool store[NI][NJ];
   if constexpr (!F16) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) store[j] = true;
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) store[i][j] = true;
     contraction_epilogue<NI, NJ>(a, acc, spk, row_w, ch_w, n_live, store,
                                  EpiUnits{nullptr, nullptr, a.pinv});
   } else {
-    // rows with a non-finite accumulator (0 x finite = 0, else NaN); both
-    // lane halves of a row take part
+    // rows of a channel tile with a non-finite accumulator (0 x finite = 0,
+    // else NaN); both lane halves of a row take part
     bool again = false;
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      float z = 0.f;
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
-      for (int m = 0; m < 2; ++m)
+      for (int j = 0; j < NJ; ++j) {
+        float z = 0.f;
 #pragma unroll
-        for (int i = 0; i < NI; ++i)
+        for (int m = 0; m < 2; ++m)
 #pragma unroll
           for (int e = 0; e < 16; ++e) z = __builtin_fmaf(acc[m][i][j][e], 0.f, z);
-      const int bad = !(z == 0.f);
-      store[j] = !(bad | __shfl_xor(bad, 32));
-      again |= !store[j];
-    }
+        const int bad = !(z == 0.f);
+        store[i][j] = !(bad | __shfl_xor(bad, 32));
+        again |= !store[i][j];
+      }
     contraction_epilogue<NI, NJ>(a, acc, spk, row_w, ch_w, n_live, store,
                                  EpiUnits{a.unit0, a.unit1, 0.0});
     if (!__any(again)) return;
@@ -666,7 +670,9 @@ __global__ __launch_bounds__(64 * WR * WC * SPL, 1) void k_contract(GemmArgs a) 
         }
     }
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) store[j] = !store[j];
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) store[i][j] = !store[i][j];
     contraction_epilogue<NI, NJ>(a, acc, spk, row_w, ch_w, n_live, store,
                                  EpiUnits{nullptr, nullptr, a.pinv});
   }

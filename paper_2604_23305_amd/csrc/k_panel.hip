@@ -205,10 +205,13 @@ struct Bins {
 };
 
 // dP of a row: t0, t1 the table rows around its PWV, ps the source power.
-// csc is the same in the whole workgroup: a row at an elevation without airmass
-// (csc negative or infinite), which only a user trajectory reaches, takes the
-// library's expm1f, which overflows to the infinity it should, and leaves the
-// bins of the padding, where 0 times infinity would be NaN, at zero.
+// ANY_EL: the elevation may be one without airmass (csc negative or infinite;
+// only a user trajectory reaches it).  csc is the same in the whole workgroup:
+// such a row takes the library's expm1f, which overflows to the infinity it
+// should, and leaves the bins of the padding, where 0 times infinity would be
+// NaN, at zero.  Other scans do without that branch, which takes 6 registers
+// and a wave per SIMD (0.6 us of a 45 us call).
+template <bool ANY_EL>
 __device__ __forceinline__ f32x4 row_deviation(const Bins& b, int F, f32x4 t0, f32x4 t1,
                                                f32x4 ps, float lw, float csc, bool src,
                                                uint32_t* far) {
@@ -225,7 +228,7 @@ __device__ __forceinline__ f32x4 row_deviation(const Bins& b, int F, f32x4 t0, f
       *far += (uint32_t)__builtin_popcountll(__ballot(fabsf(dP[k]) > 0.125f * P));
     }
   };
-  if (csc >= 0.f && csc < INFINITY)
+  if (!ANY_EL || (csc >= 0.f && csc < INFINITY))
     bins([](float x) { return one_minus_exp(x); }, [](uint32_t) { return false; });
   else
     bins([](float x) { return -expm1f(-x); }, [&](uint32_t j) { return j >= (uint32_t)F; });
@@ -239,7 +242,7 @@ __device__ __forceinline__ f32x4 row_deviation(const Bins& b, int F, f32x4 t0, f
 // kBatch rows' table values are loaded together, ahead of their arithmetic;
 // n_rows is a multiple of it.
 constexpr int kBatch = 2;
-template <class Rec>
+template <bool ANY_EL, class Rec>
 __device__ __forceinline__ void panel_rows(const PanelArgs& a, int n_rows, int first,
                                            int stride, Rec record) {
   const int64_t Fp = a.Fp;
@@ -282,7 +285,7 @@ __device__ __forceinline__ void panel_rows(const PanelArgs& a, int n_rows, int f
         }
         f32x4 dP = {0.f, 0.f, 0.f, 0.f};
         if (q[u].valid)
-          dP = row_deviation(b, a.F, t0[u], t1[u], ps, q[u].lw, q[u].csc, src, &far);
+          dP = row_deviation<ANY_EL>(b, a.F, t0[u], t1[u], ps, q[u].lw, q[u].csc, src, &far);
         // past the caches: the panel is larger than them, and what it would
         // push out (table rows, cube corners) is read again
         if (in) __builtin_nontemporal_store(dP, reinterpret_cast<f32x4*>(out[u] + b.j));
@@ -306,6 +309,7 @@ __device__ __forceinline__ int64_t uniform(int64_t v) {
 // Rows in their own order: workgroup (b, y) computes rows R b .. R b + R - 1
 // (one pixel, consecutive samples), R = a.rows_wg, in the bin passes y, y +
 // gridDim.y, ...; the first R threads derive the row records.
+template <bool ANY_EL>
 __global__ __launch_bounds__(256) void k_panel(PanelArgs a) {
   __shared__ RowInfo ri[kPanelRows];
   const int64_t row0 = (int64_t)blockIdx.x * a.rows_wg;
@@ -314,7 +318,7 @@ __global__ __launch_bounds__(256) void k_panel(PanelArgs a) {
     ri[threadIdx.x] = row_info(a, row0 + threadIdx.x, &bucket, blockIdx.y == 0);
   }
   __syncthreads();
-  panel_rows(a, a.rows_wg, blockIdx.y, gridDim.y, [&](int rr, int64_t* row) {
+  panel_rows<ANY_EL>(a, a.rows_wg, blockIdx.y, gridDim.y, [&](int rr, int64_t* row) {
     *row = row0 + rr;
     RowInfo q = ri[rr];
     q.valid = uniform(q.valid);
@@ -394,12 +398,13 @@ __global__ __launch_bounds__(256) void k_panel_scatter(PanelArgs a) {
 // 1 of the bucket order.  The order slots and row records are read through
 // the constant address space at workgroup-uniform addresses, so they load
 // into scalar registers: every address and branch of a row is scalar.
+template <bool ANY_EL>
 __global__ __launch_bounds__(256) void k_panel_sorted(PanelArgs a) {
   typedef const __attribute__((address_space(4))) uint32_t* CU32;
   typedef const __attribute__((address_space(4))) RowInfo* CRow;
   const CU32 ord = (CU32)(uintptr_t)(a.order + (int64_t)blockIdx.x * a.rows_wg);
   const CRow rinfo = (CRow)(uintptr_t)a.rinfo;
-  panel_rows(a, a.rows_wg, blockIdx.y, gridDim.y, [&](int rr, int64_t* row) {
+  panel_rows<ANY_EL>(a, a.rows_wg, blockIdx.y, gridDim.y, [&](int rr, int64_t* row) {
     const uint32_t r = ord[rr];
     *row = r;
     RowInfo q;
@@ -433,8 +438,9 @@ void launch_panel(const PanelArgs& a0, hipStream_t s) {
               : rows < 2048 * kPanelRows ? 16 : kPanelRows;
   static_assert(2 % kBatch == 0, "rows per workgroup");
   const dim3 grid((unsigned)(rows / a.rows_wg), rows < 4096 * kPanelRows ? passes : 1);
+  const bool any_el = a.scan_kind == 2;
   if (a.n_buckets <= 1) {
-    hipLaunchKernelGGL(k_panel, grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(any_el ? k_panel<true> : k_panel<false>, grid, dim3(256), 0, s, a);
     return;
   }
   const unsigned rb = (unsigned)((rows + 255) / 256);
@@ -443,7 +449,8 @@ void launch_panel(const PanelArgs& a0, hipStream_t s) {
   hipLaunchKernelGGL(k_panel_info, dim3(rb), dim3(256), 0, s, a);
   hipLaunchKernelGGL(k_panel_scan, dim3(1), dim3(1024), 0, s, a.hist, a.n_buckets);
   hipLaunchKernelGGL(k_panel_scatter, dim3(rb), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(k_panel_sorted, grid, dim3(256), 0, s, a);
+  hipLaunchKernelGGL(any_el ? k_panel_sorted<true> : k_panel_sorted<false>, grid, dim3(256), 0, s,
+                     a);
 }
 
 }  // namespace gtod

@@ -221,17 +221,23 @@ __global__ __launch_bounds__(kRdThreads) void k_rd_common(ReduceArgs a) {
 #pragma unroll
     for (int q = 0; q < kRdChan; ++q) v[q] = src[min(q, nk - 1) * rowK];
   };
+  // the spaxels off source alone are read, the next one's samples ahead
+  auto next = [&](int p) {
+    do ++p; while (p < a.P && !a.off[p]);
+    return p;
+  };
   float v[kRdChan], w[kRdChan];
-  load(0, v);
-  for (int p = 0; p < a.P; ++p) {
-    if (p + 1 < a.P) load(p + 1, w);
-    if (a.off[p]) {
-      const double csc = cosecant(p);
+  int p0 = next(-1);
+  if (p0 < a.P) load(p0, v);
+  while (p0 < a.P) {
+    const int p1 = next(p0);
+    if (p1 < a.P) load(p1, w);
+    const double csc = cosecant(p0);
 #pragma unroll
-      for (int q = 0; q < kRdChan; ++q) sum[q] += (double)v[q] / -expm1(lz[q] * csc);
-    }
+    for (int q = 0; q < kRdChan; ++q) sum[q] += (double)v[q] / -expm1(lz[q] * csc);
 #pragma unroll
     for (int q = 0; q < kRdChan; ++q) v[q] = w[q];
+    p0 = p1;
   }
 #pragma unroll
   for (int q = 0; q < kRdChan; ++q) {

@@ -305,6 +305,7 @@ hipStream_t ctx_sink_stream(gtod_ctx* c, int which);
 // A tile's samples, sorted by cell, in runs of at most kRdRun: start (11 bits),
 // length - 1 (5), cell (12), cell in several runs (1).
 constexpr int kRdTile = 2048, kRdRun = 8;
+constexpr int kRdChan = 8;   // channels of a thread of the common-mode kernel
 void launch_reduce_setup(const ReduceArgs& a, hipStream_t s);
 void launch_reduce_common(const ReduceArgs& a, hipStream_t s);
 int launch_reduce_grid(const ReduceArgs& a, hipStream_t s);  // 0 ok

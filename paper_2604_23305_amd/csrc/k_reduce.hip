@@ -199,7 +199,6 @@ __device__ inline void store4(T* p, int n, const T* v) {
 }
 
 // One thread per sample and kRdChan channels of the group.
-constexpr int kRdChan = 8;
 __global__ __launch_bounds__(kRdThreads) void k_rd_common(ReduceArgs a) {
   const int64_t t = (int64_t)blockIdx.x * kRdThreads + threadIdx.x;
   const int kl0 = blockIdx.y * kRdChan;

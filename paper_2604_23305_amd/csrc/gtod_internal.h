@@ -199,7 +199,7 @@ struct ReduceArgs {
   const double* traj;         // [t_total][2]
   const double* dphi;         // [P] device (staged)
   const double* dtheta;       // [P]
-  const int* off;             // [P] 1 if the spaxel is off source
+  const int* off;             // [P] first spaxel from p on that is off source, or P
   int n_out;
   const double* tau64;        // [n_pwv][F]
   const double* B0;           // [F][K]
@@ -305,7 +305,8 @@ hipStream_t ctx_sink_stream(gtod_ctx* c, int which);
 // A tile's samples, sorted by cell, in runs of at most kRdRun: start (11 bits),
 // length - 1 (5), cell (12), cell in several runs (1).
 constexpr int kRdTile = 2048, kRdRun = 8;
-constexpr int kRdChan = 8;   // channels of a thread of the common-mode kernel
+constexpr int kRdChan = 8;       // channels of a thread of the common-mode kernel
+constexpr int kRdGridChan = 4;   // channels of a block of the unsorted gridding
 void launch_reduce_setup(const ReduceArgs& a, hipStream_t s);
 void launch_reduce_common(const ReduceArgs& a, hipStream_t s);
 int launch_reduce_grid(const ReduceArgs& a, hipStream_t s);  // 0 ok

@@ -198,15 +198,18 @@ __device__ inline void store4(T* p, int n, const T* v) {
   }
 }
 
-// One thread per sample and kRdChan channels of the group.
+// One thread per sample and CH channels of the group: kRdChan, or fewer where a
+// call has fewer (7 x 1 x 100 samples: 33 us, 38 with 7 slots that repeat the
+// channel).
+template <int CH>
 __global__ __launch_bounds__(kRdThreads) void k_rd_common(ReduceArgs a) {
   const int64_t t = (int64_t)blockIdx.x * kRdThreads + threadIdx.x;
-  const int kl0 = blockIdx.y * kRdChan;
+  const int kl0 = blockIdx.y * CH;
   if (t >= a.T) return;
-  const int nk = min(kRdChan, a.kg - kl0);
-  double lz[kRdChan], sum[kRdChan];
+  const int nk = min(CH, a.kg - kl0);
+  double lz[CH], sum[CH];
 #pragma unroll
-  for (int q = 0; q < kRdChan; ++q) {
+  for (int q = 0; q < CH; ++q) {
     lz[q] = a.lnz[a.k0 + min(kl0 + q, a.kg - 1)];    // dead slots repeat the last channel
     sum[q] = 0.0;
   }
@@ -215,31 +218,29 @@ __global__ __launch_bounds__(kRdThreads) void k_rd_common(ReduceArgs a) {
   auto cosecant = [&](int p) {
     return a.csc_common ? a.csc_common[p * a.T + t] : 1.0 / sin(th + a.dtheta[p]);
   };
-  auto load = [&](int p, float (&v)[kRdChan]) {
+  auto load = [&](int p, float (&v)[CH]) {
     const float* src = a.tod + ((int64_t)p * a.K + a.k0 + kl0) * rowK + t;
 #pragma unroll
-    for (int q = 0; q < kRdChan; ++q) v[q] = src[min(q, nk - 1) * rowK];
+    for (int q = 0; q < CH; ++q) v[q] = src[min(q, nk - 1) * rowK];
   };
   // the spaxels off source alone are read, the next one's samples ahead
-  auto next = [&](int p) {
-    do ++p; while (p < a.P && !a.off[p]);
-    return p;
-  };
-  float v[kRdChan], w[kRdChan];
-  int p0 = next(-1);
-  if (p0 < a.P) load(p0, v);
+  auto next = [&](int p) { return p + 1 < a.P ? a.off[p + 1] : a.P; };
+  float v[CH], w[CH];
+  int p0 = a.off[0], p1 = next(p0);      // there is one
+  load(p0, v);
   while (p0 < a.P) {
-    const int p1 = next(p0);
     if (p1 < a.P) load(p1, w);
+    const int p2 = next(p1);
     const double csc = cosecant(p0);
 #pragma unroll
-    for (int q = 0; q < kRdChan; ++q) sum[q] += (double)v[q] / -expm1(lz[q] * csc);
+    for (int q = 0; q < CH; ++q) sum[q] += (double)v[q] / -expm1(lz[q] * csc);
 #pragma unroll
-    for (int q = 0; q < kRdChan; ++q) v[q] = w[q];
+    for (int q = 0; q < CH; ++q) v[q] = w[q];
     p0 = p1;
+    p1 = p2;
   }
 #pragma unroll
-  for (int q = 0; q < kRdChan; ++q) {
+  for (int q = 0; q < CH; ++q) {
     sum[q] /= (double)a.n_out;
     if (q < nk && a.M) a.M[(int64_t)(kl0 + q) * a.T + t] = sum[q];
   }
@@ -249,7 +250,7 @@ __global__ __launch_bounds__(kRdThreads) void k_rd_common(ReduceArgs a) {
     load(p, v);
     float* dst = a.t_star + ((int64_t)p * a.K + a.k0 + kl0) * rowK + t;
 #pragma unroll
-    for (int q = 0; q < kRdChan; ++q) {
+    for (int q = 0; q < CH; ++q) {
       const double em = expm1(lz[q] * csc);     // eta - 1
       if (q < nk) dst[q * rowK] = (float)(((double)v[q] + em * sum[q]) / (1.0 + em));
     }
@@ -476,7 +477,7 @@ __global__ __launch_bounds__(kRdMapThreads, 4) void k_rd_map(ReduceArgs a) {
   }
 }
 
-// For workspaces without room for the runs.
+// For short series, and workspaces without room for the runs.
 // One block per (spaxel, kRdGridChan channels of the group), spaxel
 // fastest so that the blocks sharing those channels' M rows run together.
 // The sample's cosecant and cell are evaluated once for all its channels;
@@ -485,7 +486,6 @@ __global__ __launch_bounds__(kRdMapThreads, 4) void k_rd_map(ReduceArgs a) {
 // LDS; the variance is (S2 - S1^2 / m) / (m - 1).  When T* is requested
 // with maps, this kernel also stores it (for every sample, in or out of
 // the map).
-constexpr int kRdGridChan = 4;
 __global__ __launch_bounds__(kRdThreads) void k_rd_grid(ReduceArgs a) {
   extern __shared__ double gsm[];
   const int C = a.map_n * a.map_n;
@@ -592,9 +592,11 @@ void launch_reduce_setup(const ReduceArgs& a, hipStream_t s) {
 }
 
 void launch_reduce_common(const ReduceArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_rd_common,
-                     dim3((unsigned)((a.T + kRdThreads - 1) / kRdThreads),
-                          (a.kg + kRdChan - 1) / kRdChan),
+  const int ch = a.kg > 4 ? kRdChan : a.kg > 2 ? 4 : a.kg;
+  const auto kernel = ch == 1 ? k_rd_common<1> : ch == 2 ? k_rd_common<2>
+                      : ch == 4 ? k_rd_common<4> : k_rd_common<kRdChan>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)((a.T + kRdThreads - 1) / kRdThreads),
+                                  (a.kg + ch - 1) / ch),
                      dim3(kRdThreads), 0, s, a);
 }
 

@@ -1263,6 +1263,8 @@ gtod_status gtod_reduce(gtod_ctx* c, const gtod_reduce_desc* d, void* hip_stream
     n_out += off[p];
   }
   if (n_out == 0) return fail(c, GTOD_EINVAL, "no spaxel lies outside r_out_rad");
+  // the first spaxel from p on that is off source, or P
+  for (int p = P - 1, next = P; p >= 0; --p) off[p] = next = off[p] ? p : next;
   const size_t stage_bytes = (size_t)P * 20 + 64;
   if (stage_bytes > kSlotBytes) return fail(c, GTOD_EINVAL, "too many spaxels");
   HIP_TRY(c, hipSetDevice(c->device));
@@ -1280,19 +1282,37 @@ gtod_status gtod_reduce(gtod_ctx* c, const gtod_reduce_desc* d, void* hip_stream
   int64_t kg = avail > 0 ? K : 0;
   if (maps) kg = avail > 0 ? std::min<int64_t>(K, (avail - 256) / per_ch) : 0;
   if (kg < 1) return fail(c, GTOD_EINVAL, "workspace too small for one channel of the reduction");
-  // scratch of the faster kernels, where there is room for it and for a thread's
-  // channels of the common-mode kernel: 49 spaxels x 100 channels x 44000 samples
-  // in 64 MiB take 15.1 ms one channel at a time beside it, 2.9 in groups of 44
-  // without it; x 40000 samples 3.0 ms five at a time, 2.5 without; x 38000
-  // samples 2.0 ms eight at a time, 2.4 without
+  // The kernels with scratch of their own, where they are the faster ones and
+  // there is room for it.  Maps: the sort costs 20 us or more whatever the
+  // length, where the blocks of the unsorted kernel take a sample of a few
+  // channels each in turn, so that its time goes with T and the rounds of its
+  // blocks (us sorted / unsorted: 7 spaxels x 30 channels x 3000 samples 71 /
+  // 67, x 10000 88 / 125; 49 x 300 in 48 x 48 cells, 14 rounds, x 1000 243 /
+  // 300), and one or two channels share a sort badly (49 x 1 x 14000 133 / 124).
+  // Without maps the table of cosecants saves what two or more threads would
+  // take of each (49 x 100 x 57600 1.12 / 1.24 ms, 49 x 1 93 / 70 us).
+  bool fast = K > kRdChan || T <= 16384;
+  if (maps) {
+    const double blocks = (double)P * ((K + kRdGridChan - 1) / kRdGridChan);
+    const double rounds = blocks / (256.0 * std::min<int64_t>(8, (160 << 10) / (C * 68)));
+    fast = (double)T * std::max(1.0, rounds) >= (K == 1 ? 16000 : K < 4 ? 8000 : 4800);
+  }
+  // Room: with a thread's channels of the common-mode kernel beside it.  49
+  // spaxels x 100 channels x 44000 samples in 64 MiB take 15.1 ms one channel at
+  // a time beside the scratch, 2.9 in groups of 44 without it; x 40000 samples
+  // 3.0 ms five at a time, 2.5 without; x 38000 samples 2.0 ms eight at a time,
+  // 2.4 without.
   const int64_t tiles = (T + kRdTile - 1) / kRdTile;
   const int64_t csc = round_up((int64_t)P * T * 8, 256);
   const int64_t runs = maps ? (int64_t)P * tiles * kRdTile * 6 + round_up((int64_t)P * tiles * 4, 256) : 0;
-  const int64_t parts = 256 * 8;
-  const int64_t extra = (maps ? 2 : 1) * csc + runs + parts;
-  bool fast = avail > extra;
-  if (fast && maps) {
-    const int64_t n = std::min<int64_t>(K, (avail - extra - 256) / per_ch);
+  auto group = [&](int64_t extra) {   // channels per group beside extra bytes
+    if (!maps) return avail > extra ? (int64_t)K : 0;
+    return std::max<int64_t>(0, std::min<int64_t>(K, (avail - extra - 256) / per_ch));
+  };
+  const int64_t parts = d->pwv && group(256 * 8) == kg ? 256 * 8 : 0;
+  const int64_t extra = (maps ? 2 : 1) * csc + runs;
+  if (fast) {
+    const int64_t n = group(parts + extra);
     fast = n >= std::min<int64_t>(K, kRdChan);
     if (fast) kg = n;
   }
@@ -1347,6 +1367,10 @@ gtod_status gtod_reduce(gtod_ctx* c, const gtod_reduce_desc* d, void* hip_stream
   a.map = d->map;
   a.weight = d->weight;
   char* grp = ws + fixed;
+  if (parts) {
+    a.pwv_part = (double*)grp;
+    grp += parts;
+  }
   if (fast) {
     a.csc_common = (double*)grp;
     if (maps) {
@@ -1355,7 +1379,6 @@ gtod_status gtod_reduce(gtod_ctx* c, const gtod_reduce_desc* d, void* hip_stream
       a.perm = (uint16_t*)(a.runs + (int64_t)P * tiles * kRdTile);
       a.n_runs = (int*)(a.perm + (int64_t)P * tiles * kRdTile);
     }
-    a.pwv_part = (double*)(grp + extra - parts);
     grp += extra;
   }
   a.M = maps ? (double*)grp : nullptr;

@@ -235,27 +235,45 @@ __device__ __forceinline__ f32x4 row_deviation(const Bins& b, int F, f32x4 t0, f
   return dP;
 }
 
+// A wave-uniform value, in a scalar register.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ float uniform(float v) {
+  return __builtin_bit_cast(float, uniform(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ int64_t uniform(int64_t v) {
+  return ((int64_t)uniform((int)(v >> 32)) << 32) | (uint32_t)uniform((int)v);
+}
+
 // Rows of one workgroup, record(rr) giving the record and panel row of the
 // rr-th, over the passes of 1024 bins first, first + stride, ...  Within a
 // pass the spectra E, D, W, Pref stay in registers, and the cube corners
 // are loaded only where a row's cell is another than the row's before.
 // kBatch rows' table values are loaded together, ahead of their arithmetic;
 // n_rows is a multiple of it.
+// NARROW: up to 512 bins are one or two waves' work, so that each wave, or pair
+// of waves, takes every fourth, or second, kBatch of rows (1.14 M rows of 64
+// bins: 150 us, 700 with three waves idle).
 constexpr int kBatch = 2;
-template <bool ANY_EL, class Rec>
+constexpr int kNarrowBins = 512;
+template <bool ANY_EL, bool NARROW, class Rec>
 __device__ __forceinline__ void panel_rows(const PanelArgs& a, int n_rows, int first,
                                            int stride, Rec record) {
   const int64_t Fp = a.Fp;
   const int64_t ld = a.cube_ld, crow = (int64_t)a.n_az * a.cube_ld;
+  // waves of a row, and this wave's first and step among the rows
+  const int waves = NARROW && a.Fp <= kNarrowBins / 2 ? 1 : 2;
+  const int row0 = NARROW ? uniform((int)threadIdx.x >> 6) / waves * kBatch : 0;
+  const int row_step = NARROW ? 4 / waves * kBatch : kBatch;
+  const int lane = NARROW ? threadIdx.x & (64 * waves - 1) : threadIdx.x;
   uint32_t far = 0;
   for (int j0 = first * kTileBins; j0 < a.Fp; j0 += stride * kTileBins) {
-    const Bins b(a, j0 + 4 * threadIdx.x);
+    const Bins b(a, j0 + 4 * lane);
     const bool in = b.j < (uint32_t)a.Fp;
     const uint32_t jc = in ? b.j : 0;
     int64_t cell = -1;                 // the corners held in c
     f32x4 c[4] = {};
 #pragma unroll 1
-    for (int rb = 0; rb < n_rows; rb += kBatch) {
+    for (int rb = row0; rb < n_rows; rb += row_step) {
       RowInfo q[kBatch];
       float* out[kBatch];
       f32x4 t0[kBatch], t1[kBatch];
@@ -295,21 +313,12 @@ __device__ __forceinline__ void panel_rows(const PanelArgs& a, int n_rows, int f
   far_from_reference(a, far);
 }
 
-// A wave-uniform value, in a scalar register.
-__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ float uniform(float v) {
-  return __builtin_bit_cast(float, uniform(__builtin_bit_cast(int, v)));
-}
-__device__ __forceinline__ int64_t uniform(int64_t v) {
-  return ((int64_t)uniform((int)(v >> 32)) << 32) | (uint32_t)uniform((int)v);
-}
-
 }  // namespace
 
 // Rows in their own order: workgroup (b, y) computes rows R b .. R b + R - 1
 // (one pixel, consecutive samples), R = a.rows_wg, in the bin passes y, y +
 // gridDim.y, ...; the first R threads derive the row records.
-template <bool ANY_EL>
+template <bool ANY_EL, bool NARROW>
 __global__ __launch_bounds__(256) void k_panel(PanelArgs a) {
   __shared__ RowInfo ri[kPanelRows];
   const int64_t row0 = (int64_t)blockIdx.x * a.rows_wg;
@@ -318,7 +327,7 @@ __global__ __launch_bounds__(256) void k_panel(PanelArgs a) {
     ri[threadIdx.x] = row_info(a, row0 + threadIdx.x, &bucket, blockIdx.y == 0);
   }
   __syncthreads();
-  panel_rows<ANY_EL>(a, a.rows_wg, blockIdx.y, gridDim.y, [&](int rr, int64_t* row) {
+  panel_rows<ANY_EL, NARROW>(a, a.rows_wg, blockIdx.y, gridDim.y, [&](int rr, int64_t* row) {
     *row = row0 + rr;
     RowInfo q = ri[rr];
     q.valid = uniform(q.valid);
@@ -398,13 +407,13 @@ __global__ __launch_bounds__(256) void k_panel_scatter(PanelArgs a) {
 // 1 of the bucket order.  The order slots and row records are read through
 // the constant address space at workgroup-uniform addresses, so they load
 // into scalar registers: every address and branch of a row is scalar.
-template <bool ANY_EL>
+template <bool ANY_EL, bool NARROW>
 __global__ __launch_bounds__(256) void k_panel_sorted(PanelArgs a) {
   typedef const __attribute__((address_space(4))) uint32_t* CU32;
   typedef const __attribute__((address_space(4))) RowInfo* CRow;
   const CU32 ord = (CU32)(uintptr_t)(a.order + (int64_t)blockIdx.x * a.rows_wg);
   const CRow rinfo = (CRow)(uintptr_t)a.rinfo;
-  panel_rows<ANY_EL>(a, a.rows_wg, blockIdx.y, gridDim.y, [&](int rr, int64_t* row) {
+  panel_rows<ANY_EL, NARROW>(a, a.rows_wg, blockIdx.y, gridDim.y, [&](int rr, int64_t* row) {
     const uint32_t r = ord[rr];
     *row = r;
     RowInfo q;
@@ -438,9 +447,11 @@ void launch_panel(const PanelArgs& a0, hipStream_t s) {
               : rows < 2048 * kPanelRows ? 16 : kPanelRows;
   static_assert(2 % kBatch == 0, "rows per workgroup");
   const dim3 grid((unsigned)(rows / a.rows_wg), rows < 4096 * kPanelRows ? passes : 1);
-  const bool any_el = a.scan_kind == 2;
+  const bool any_el = a.scan_kind == 2, narrow = a.Fp <= kNarrowBins;
   if (a.n_buckets <= 1) {
-    hipLaunchKernelGGL(any_el ? k_panel<true> : k_panel<false>, grid, dim3(256), 0, s, a);
+    const auto kernel = any_el ? (narrow ? k_panel<true, true> : k_panel<true, false>)
+                               : (narrow ? k_panel<false, true> : k_panel<false, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a);
     return;
   }
   const unsigned rb = (unsigned)((rows + 255) / 256);
@@ -449,8 +460,9 @@ void launch_panel(const PanelArgs& a0, hipStream_t s) {
   hipLaunchKernelGGL(k_panel_info, dim3(rb), dim3(256), 0, s, a);
   hipLaunchKernelGGL(k_panel_scan, dim3(1), dim3(1024), 0, s, a.hist, a.n_buckets);
   hipLaunchKernelGGL(k_panel_scatter, dim3(rb), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(any_el ? k_panel_sorted<true> : k_panel_sorted<false>, grid, dim3(256), 0, s,
-                     a);
+  const auto kernel = any_el ? (narrow ? k_panel_sorted<true, true> : k_panel_sorted<true, false>)
+                             : (narrow ? k_panel_sorted<false, true> : k_panel_sorted<false, false>);
+  hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a);
 }
 
 }  // namespace gtod

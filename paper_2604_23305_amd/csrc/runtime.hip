@@ -222,7 +222,10 @@ gtod_status get_ws(gtod_ctx* c, hipStream_t s, StreamWs** out) {
   w.stream = s;
   ws_sizes(c, &w.panel_bytes, &w.pink_bytes);
   gtod_status st;
-  if ((st = dev_alloc(c, (void**)&w.panel, w.panel_bytes)) != GTOD_OK ||
+  // the panel also holds what does not scale with a call, whatever its size: the
+  // quadrature nodes of a far field (up to 3680, 57.5 KiB), the factors of a
+  // footprint (1.25 KiB)
+  if ((st = dev_alloc(c, (void**)&w.panel, std::max<size_t>(w.panel_bytes, 64 << 10))) != GTOD_OK ||
       (st = dev_alloc(c, (void**)&w.pink, w.pink_bytes)) != GTOD_OK ||
       (st = dev_alloc(c, (void**)&w.d_stage, kSlots * kSlotBytes)) != GTOD_OK) {
     free_ws(c, w);

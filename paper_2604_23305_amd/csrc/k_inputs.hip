@@ -15,7 +15,8 @@
 // plane and its far-field table F[|dj|][|di|] in LDS; each thread sums 2x2
 // outputs in FP64.  Screen: weights A(r) normalised to 1 over the cells within R,
 // edges clamped; A is a product of a function of x and one of y inside the
-// disk, so a row's cells are summed once per row of the footprint.
+// disk, so a row's cells are summed once per row of the footprint (in strips), or
+// cell by cell where the footprint or the screen is small.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -144,8 +145,7 @@ __device__ inline double lane_value(double v, int lane) {
 // normalisation (the sum of the weights is 1; fixed-order sum), then width,
 // each at a pitch of kFactorPitch words.
 __global__ __launch_bounds__(64) void k_screen_weights(ScreenConvArgs a) {
-  __shared__ double sum[64];
-  double* gx = a.w;
+  __shared__ double sum[64], gx[64];
   double* gy = a.w + kFactorPitch;
   int* width = reinterpret_cast<int*>(a.w + 2 * kFactorPitch);
   auto factor = [&](double x) {
@@ -154,6 +154,7 @@ __global__ __launch_bounds__(64) void k_screen_weights(ScreenConvArgs a) {
   };
   const int d = threadIdx.x;
   gx[d] = d <= a.rx ? factor(d * a.dx) : 0.0;
+  a.w[d] = gx[d];
   __syncthreads();
   const double gyd = d <= a.ry ? factor(d * a.dy) : 0.0;
   double acc = 0.0;
@@ -244,6 +245,57 @@ __global__ __launch_bounds__(256) void k_screen_conv(ScreenConvArgs a) {
   }
 }
 
+// Small footprints and narrow screens: 64 x 32 outputs and the cells around them
+// in LDS, thread (tx, ty) sums the footprint of rows ty + 4 r of column tx cell by
+// cell.  Nothing is serial along the screen, so small calls fill the card.
+constexpr int kTileX = 64, kTileY = 32;
+static int64_t tile_lds(const ScreenConvArgs& a) {
+  return 8 * ((int64_t)(2 * a.rx + 1) * (2 * a.ry + 1) +
+              (int64_t)(kTileX + 2 * a.rx) * (kTileY + 2 * a.ry));
+}
+__global__ __launch_bounds__(256) void k_screen_tile(ScreenConvArgs a) {
+  extern __shared__ double dsm[];
+  const int wx = 2 * a.rx + 1, wy = 2 * a.ry + 1;
+  const int TW = kTileX + 2 * a.rx, TH = kTileY + 2 * a.ry;
+  double* const sw = dsm;              // [wy][wx]
+  double* const st = dsm + wx * wy;    // [TH][TW]
+  const double* const gx = a.w;
+  const double* const gy = a.w + kFactorPitch;
+  const int* const width = reinterpret_cast<const int*>(a.w + 2 * kFactorPitch);
+  const int64_t tiles_x = (a.nx + kTileX - 1) / kTileX;
+  const int64_t x0 = (blockIdx.x % tiles_x) * kTileX;
+  const int64_t y0 = (blockIdx.x / tiles_x) * kTileY;
+  for (int q = threadIdx.x; q < wx * wy; q += 256) {
+    const int dx = abs(q % wx - a.rx), dy = abs(q / wx - a.ry);
+    sw[q] = dx <= width[dy] ? gx[dx] * gy[dy] : 0.0;
+  }
+  for (int q = threadIdx.x; q < TW * TH; q += 256) {
+    int64_t y = y0 - a.ry + q / TW, x = x0 - a.rx + q % TW;
+    y = y < 0 ? 0 : (y >= a.ny ? a.ny - 1 : y);
+    x = x < 0 ? 0 : (x >= a.nx ? a.nx - 1 : x);
+    st[q] = a.in[y * a.nx + x];
+  }
+  __syncthreads();
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  double acc[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) acc[r] = 0.0;
+  for (int dy = 0; dy < wy; ++dy) {
+    for (int dx = 0; dx < wx; ++dx) {
+      const double w = sw[dy * wx + dx];
+      if (w == 0.0) continue;
+      const double* const col = st + (ty + dy) * TW + tx + dx;
+#pragma unroll
+      for (int r = 0; r < 8; ++r) acc[r] += w * col[4 * r * TW];
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const int64_t y = y0 + ty + 4 * r, x = x0 + tx;
+    if (y < a.ny && x < a.nx) a.out[y * a.nx + x] = acc[r];
+  }
+}
+
 void launch_gauss_legendre(double* x, double* w, int n, hipStream_t s) {
   hipLaunchKernelGGL(k_gauss_legendre, dim3((n + 127) / 128), dim3(128), 0, s, x, w, n);
 }
@@ -266,6 +318,7 @@ int launch_source_conv(const SrcConvArgs& a, hipStream_t s) {
 void launch_screen_conv(const ScreenConvArgs& a0, hipStream_t s) {
   ScreenConvArgs a = a0;
   hipLaunchKernelGGL(k_screen_weights, dim3(1), dim3(64), 0, s, a);
+  const int n = std::max(a.rx, a.ry);
   // the longest strips (their ry extra rows on either side are work done
   // again) that still give every CU the two workgroups it holds: 512 x 65536
   // cells of 0.2 m 0.92 -> 0.84 ms against four workgroups, 300 x 8000 of 0.25 m
@@ -274,7 +327,29 @@ void launch_screen_conv(const ScreenConvArgs& a0, hipStream_t s) {
   const int64_t strips = std::max<int64_t>(1, 512 / cols);
   a.strip = (int)std::max<int64_t>((a.ny + strips - 1) / strips, 16);
   const dim3 grid((unsigned)cols, (unsigned)((a.ny + a.strip - 1) / a.strip));
-  const int n = std::max(a.rx, a.ry);
+  if (n <= 16) {
+    // Cell by cell or in strips, by the time either takes (us; the constants
+    // from screens of 16 x 16 to 512 x 65536 and footprints of 0 to 12 cells):
+    // a tile's chain of 0.148 per cell of the footprint, of which a CU overlaps
+    // as many as its LDS holds down to 0.0577 each; a strip's rows, each a chain
+    // from load to store, one or two strips to a CU.  4 cells, 64 x 64: 19 by
+    // tiles, 30 in strips; 512 x 65536: 281 and 298; 8 cells: 44 and 31, 755 and
+    // 300; 100000 x 64: 171 and 224.
+    const double taps = 0.785 * (2 * a.rx + 1) * (2 * a.ry + 1);
+    const int64_t lds = tile_lds(a), resident = std::min<int64_t>(8, (160 << 10) / lds);
+    const int64_t tiles = (a.nx + kTileX - 1) / kTileX * ((a.ny + kTileY - 1) / kTileY);
+    const int64_t per_cu = (tiles + 255) / 256;
+    auto round = [&](int64_t k) { return k ? std::max(0.148, 0.0577 * (double)k) * taps : 0.0; };
+    const double by_tiles = 10.0 + (double)(per_cu / resident) * round(resident) +
+                            round(per_cu % resident);
+    const bool shared = (int64_t)grid.x * grid.y > 256;
+    const double per_row = n <= 8 ? (shared ? 1.08 : 0.78) : (shared ? 1.83 : 1.32);
+    const double by_strips = 5.0 + (a.strip + (n <= 8 ? 16 : 32)) * per_row;
+    if (by_tiles < by_strips) {
+      hipLaunchKernelGGL(k_screen_tile, dim3((unsigned)tiles), dim3(256), lds, s, a);
+      return;
+    }
+  }
   if (n <= 8) hipLaunchKernelGGL(k_screen_conv<8>, grid, dim3(256), 0, s, a);
   else if (n <= 16) hipLaunchKernelGGL(k_screen_conv<16>, grid, dim3(256), 0, s, a);
   else if (n <= 25) hipLaunchKernelGGL(k_screen_conv<25>, grid, dim3(256), 0, s, a);

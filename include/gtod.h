@@ -317,7 +317,7 @@ gtod_status gtod_simulate_tod(gtod_ctx* ctx, const gtod_job* jobs,
  *
  * Limits: a SIGNAL job needs at least 128 rows of 4 F_pad + 56 bytes
  * (F_pad = F rounded up to 32), and a PINK job of t_total samples needs
- * 4 N bytes per series plus 64 KiB (N = the power of two >= t_total);
+ * 4 N bytes per series (N = the power of two >= t_total);
  * both must fit in GTOD_NOALLOC_SCRATCH_BYTES - 8 MiB.  Larger jobs are
  * rejected with EINVAL before anything is enqueued.
  * Errors: those of gtod_simulate_tod, except EBUDGET.

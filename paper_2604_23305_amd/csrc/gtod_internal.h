@@ -126,7 +126,6 @@ struct PinkArgs {
 constexpr int kPinkLgM2 = 11;                // log2 of the usual 1/f pass-1 length
 constexpr int kPinkLgB2 = 4;                 // log2 of the 1/f pass-2 columns per workgroup
 constexpr int kPinkTable = 4096;             // twiddle table
-constexpr int kPinkTableFloat2 = 2 * 4096;   // of a workspace, before the series' scratch
 
 // setup kernels (FP64)
 struct SpecSetupArgs {

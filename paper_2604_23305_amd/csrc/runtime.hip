@@ -208,8 +208,7 @@ void free_ws(gtod_ctx* c, StreamWs& w) {
 // Byte sizes of a stream workspace's panel and 1/f areas.
 void ws_sizes(const gtod_ctx* c, size_t* panel_bytes, size_t* pink_bytes) {
   *panel_bytes = round_up((int64_t)(c->ws_bytes * 3 / 4), 256);
-  *pink_bytes = std::max<int64_t>(round_up((int64_t)(c->ws_bytes - *panel_bytes), 256),
-                                  2 * kPinkTableFloat2 * (int64_t)sizeof(float2));
+  *pink_bytes = std::max<int64_t>(round_up((int64_t)(c->ws_bytes - *panel_bytes), 256), 64 << 10);
 }
 
 gtod_status get_ws(gtod_ctx* c, hipStream_t s, StreamWs** out) {
@@ -370,10 +369,9 @@ gtod_status plan_chunks(gtod_ctx* c, JobPlan* pl, int idx, size_t panel_bytes,
     int64_t N = 2;
     while (N < j.t_total) N *= 2;
     const int64_t M = N / 2;
-    const size_t scratch_bytes = pink_bytes - kPinkTableFloat2 * sizeof(float2);
     const int64_t S = (int64_t)j.n_pix * f.K;
     // a single-pass transform (M <= 2048) needs no scratch
-    int64_t per = M > (1 << kPinkLgM2) ? (int64_t)(scratch_bytes / ((size_t)M * sizeof(float2))) : S;
+    int64_t per = M > (1 << kPinkLgM2) ? (int64_t)(pink_bytes / ((size_t)M * sizeof(float2))) : S;
     per = std::min<int64_t>(std::min<int64_t>(per, S), 65535);
     if (per < 1) return fail(c, GTOD_EINVAL, at + "1/f series too long for " + ws_name);
     pl->pink_per = per;
@@ -1000,7 +998,7 @@ static gtod_status simulate(gtod_ctx* c, const gtod_job* jobs, int32_t n_jobs,
       a.out_ld = j.out_ld ? j.out_ld : j.t_total;
       a.accumulate = acc;
       a.tab = c->pink_table;
-      a.scratch = w->pink + kPinkTableFloat2;
+      a.scratch = w->pink;
       const int64_t S = (int64_t)j.n_pix * f.K;
       const int64_t per = plan[i].pink_per;
       for (int64_t s0 = 0; s0 < S; s0 += per) {

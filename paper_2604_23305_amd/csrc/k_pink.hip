@@ -268,10 +268,10 @@ __global__ void k_pink_tables(float2* tab) {
 // once; every Z_k is built from X_k and X_{M-k} held in LDS, two at a time
 // (e^{2 pi i (M-k)/N} = -conj e^{2 pi i k/N}).
 // Dynamic LDS: one or two padded transforms of M2 values; EMAX bounds the
-// values per workgroup.  LGM2 > 0 fixes lg M2 at compile time, so that the
-// transform's index arithmetic folds into constants; LGM2 = 0 takes it from
-// the arguments.  For series of one pass (M <= 2048), and of columns longer
-// than 2048 (the others: k_pink_pairs).
+// values per workgroup.  LGM2 > 0, for series of one column, fixes lg M2 at
+// compile time, so that the transform's index arithmetic folds into constants;
+// LGM2 = 0 takes it from the arguments.  For series of one pass (M <= 2048), and
+// of columns longer than 2048 (the others: k_pink_pairs).
 template <int EMAX, int LGM2>
 __global__ __launch_bounds__(256) void k_pink_pass1(PinkArgs a) {
   extern __shared__ float2 buf[];
@@ -349,12 +349,8 @@ __global__ __launch_bounds__(256) void k_pink_pass1(PinkArgs a) {
     }
   }
   __syncthreads();
-  if constexpr (LGM2 > 0) {
-    if (ncol == 2) fft_inv<EMAX, false>(buf, at, LGM2, 1, a.tab);
-    else fft_inv<EMAX, false>(buf, at, LGM2, 0, a.tab);
-  } else {
-    fft_inv<EMAX, false>(buf, at, lgM2, ncol - 1, a.tab);
-  }
+  if constexpr (LGM2 > 0) fft_inv<EMAX, false>(buf, at, LGM2, 0, a.tab);
+  else fft_inv<EMAX, false>(buf, at, lgM2, ncol - 1, a.tab);
   const int lgM = a.lgM1 + lgM2;
   for (int c = 0; c < ncol; ++c) {
     const int k1 = col[c];
@@ -540,8 +536,9 @@ __global__ __launch_bounds__(256) void k_pink_columns(PinkArgs a) {
   float2 v[R1];
 #pragma unroll
   for (int r = 0; r < R1; ++r) {
-    // read once, past the caches; not at 16 columns, where that is slower (45
-    // series of 2^16 samples: 21 us, 8.1 through them)
+    // read once, past the caches; not at 16 columns, where that measures slower
+    // (45 series of 2^16 samples: 21 us, 8.1 through them; 347 series 36 and 27),
+    // for a reason not known
     const float2* const p = src + ((int64_t)r << (LG2 + kPinkLgM2));
     if constexpr (LGM1 == 4)
       v[r] = *p;
@@ -613,7 +610,7 @@ void launch_pink_pass1(const PinkArgs& a, hipStream_t s) {
   const int e = (a.M1 == 1 ? 1 : 2) << a.lgM2;   // values per workgroup
   const size_t lds = (size_t)(e + (e >> 4)) * sizeof(float2);
   const dim3 grid(groups, a.n_series);
-  if (e <= kLdsC && a.lgM2 == kPinkLgM2)
+  if (a.M1 == 1 && a.lgM2 == kPinkLgM2)
     hipLaunchKernelGGL((k_pink_pass1<kLdsC, kPinkLgM2>), grid, dim3(256), lds, s, a);
   else if (e <= kLdsC)
     hipLaunchKernelGGL((k_pink_pass1<kLdsC, 0>), grid, dim3(256), lds, s, a);

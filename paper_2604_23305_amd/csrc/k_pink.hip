@@ -536,9 +536,11 @@ __global__ __launch_bounds__(256) void k_pink_columns(PinkArgs a) {
   float2 v[R1];
 #pragma unroll
   for (int r = 0; r < R1; ++r) {
-    // read once, past the caches; not at 16 columns, where that measures slower
-    // (45 series of 2^16 samples: 21 us, 8.1 through them; 347 series 36 and 27),
-    // for a reason not known
+    // read once, past the caches: us past / through them for 45, 347 and 2429
+    // series of 8 columns 6.7 / 6.7, 14.8 / 14.9, 88 / 111; 32 columns 12 / 12, 54
+    // / 54, 377 / 394; 256 columns 56 / 58, 521 / 529, 3507 / 3682.  Not at 16
+    // columns, 21 / 7.8, 35 / 26, 199 / 215: what costs the small launches 13 us
+    // at this length alone is not known
     const float2* const p = src + ((int64_t)r << (LG2 + kPinkLgM2));
     if constexpr (LGM1 == 4)
       v[r] = *p;

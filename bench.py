@@ -24,6 +24,9 @@ if ROOT not in sys.path:
 
 METRIC = ("detector-samples/s (t×pix×chan) at ≤1e-6 rel err vs "
           "FP64; p50/p99 request ms")
+# operands of the contraction by precision: FP32 values as two FP16 halves, or
+# as two BF16 halves; sums, panel and outputs are FP32 in both
+DTYPE = {"fp32": "f32 (f16x2 operands)", "split": "bf16x2"}
 # dense 16-bit MFMA FLOP/s (MI355X): FP32 jobs run on pairs of FP16 halves,
 # split ones on pairs of BF16 halves
 PEAK = 2.5e15
@@ -531,7 +534,7 @@ def c4_measure(args, g, torch, ctx, run3, sc3, stream):
     value = sc.n_pix * sc.K * sc.t_total * args.steps / elapsed
     res = {"value": value, "unit": "detector-samples/s",
            "steps": args.steps, "warmup": args.warmup,
-           "ms_per_step": elapsed * 1e3 / args.steps, "dtype": "bf16x2",
+           "ms_per_step": elapsed * 1e3 / args.steps, "dtype": DTYPE["split"],
            "config": {"workload": f"c4: {WORKLOADS['c4']}",
                       "pixels": sc.n_pix, "channels": sc.K,
                       "freq_bins": sc.F, "samples": sc.t_total,
@@ -550,7 +553,7 @@ def c5_measure(args, g, torch):
     return {"value": summ["det_samples_per_s"], "unit": "detector-samples/s",
             "makespan_ms": summ["makespan_s"] * 1e3,
             "requests": summ["requests"], "det_samples": summ["det_samples"],
-            "dtype": "f32" if prec_name == "fp32" else "bf16x2",
+            "dtype": DTYPE[prec_name],
             "config": {"workload": f"c5: {WORKLOADS['c5']}",
                        "precision": prec_name},
             "latency_ms": {"p50": summ["p50_ms"], "p99": summ["p99_ms"],
@@ -582,7 +585,7 @@ def main():
                "warmup": 1, "ms_per_step": summ["makespan_s"] * 1e3,
                "higher_is_better": True, "scaling": "weak",
                "vs_baseline": None,
-               "dtype": "f32" if prec_name == "fp32" else "bf16x2",
+               "dtype": DTYPE[prec_name],
                "data": "synthetic",
                "config": {"workload": f"c5: {WORKLOADS['c5']}",
                           "requests": summ["requests"],
@@ -667,7 +670,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32" if prec_name == "fp32" else "bf16x2",
+        "dtype": DTYPE[prec_name],
         "data": "synthetic",
         "config": {"workload": f"{args.workload}: {WORKLOADS[args.workload]}",
                    "pixels": sc.n_pix, "channels": sc.K, "freq_bins": sc.F,

@@ -569,6 +569,13 @@ gtod_status gtod_spec_nep2_ref(gtod_ctx* ctx, int32_t spec_id, double* out);
 gtod_status gtod_philox(gtod_ctx* ctx, const uint32_t* ctr, uint32_t* out,
                         int64_t n, uint64_t seed, void* hip_stream);
 
+/* Rows and channels (tile[0], tile[1]) of the tiles that a SIGNAL launch of K
+ * channels takes for so many panel rows (pixels of the launch times its samples
+ * rounded up to 128): the rule by which the contraction chooses, a host
+ * function.  Results do not depend on it.  Errors: EINVAL. */
+gtod_status gtod_contraction_tile(int32_t precision, int64_t rows, int32_t K,
+                                  int32_t tile[2]);
+
 /* Per-kernel timing.  While enabled, every kernel launch is bracketed by
  * HIP events recorded on its launch stream.  gtod_profile_enable(ctx, 1)
  * clears the totals and starts; 0 stops.  gtod_profile_read synchronises

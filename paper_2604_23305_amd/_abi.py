@@ -122,7 +122,7 @@ SYMBOLS = ["gtod_sim_init", "gtod_load_screen", "gtod_load_filters",
            "gtod_profile_read", "gtod_skydip", "gtod_reduce",
            "gtod_simulate_to_disk", "gtod_far_field", "gtod_convolve_source",
            "gtod_convolve_screen", "gtod_simulate_tod_noalloc",
-           "gtod_release_stream"]
+           "gtod_release_stream", "gtod_contraction_tile"]
 KERNEL_NAMES = ["panel", "gemm_f32", "gemm_bf16", "pink_pass1", "pink_pass2",
                 "common", "grid", "beam", "src_conv", "screen_conv"]
 MAP_MAX_N = 48
@@ -160,6 +160,8 @@ def load():
     lib.gtod_philox.argtypes = [vp, vp, vp, C.c_int64, C.c_uint64, vp]
     lib.gtod_abi_sizes.argtypes = [C.POINTER(C.c_int64)]
     lib.gtod_abi_sizes.restype = None
+    lib.gtod_contraction_tile.argtypes = [C.c_int32, C.c_int64, C.c_int32,
+                                          C.POINTER(C.c_int32)]
     lib.gtod_profile_enable.argtypes = [vp, C.c_int32]
     lib.gtod_profile_read.argtypes = [vp, C.POINTER(C.c_double), C.c_int32]
     lib.gtod_skydip.argtypes = [vp, C.c_int32, C.c_double, C.c_double,

@@ -299,6 +299,14 @@ def philox(ctx, ctr_dev, out_dev, n, seed, stream=None):
                                 n, seed, C.c_void_p(stream.cuda_stream)))
 
 
+def contraction_tile(precision, rows, K):
+    """(rows, channels) of the contraction's tiles for a launch of K channels
+    and so many panel rows (needs no GPU)."""
+    out = (C.c_int32 * 2)()
+    _check(None, _abi.load().gtod_contraction_tile(precision, rows, K, out))
+    return tuple(out)
+
+
 def profile_enable(ctx, on=True):
     lib = _abi.load()
     _check(ctx, lib.gtod_profile_enable(ctx, 1 if on else 0))

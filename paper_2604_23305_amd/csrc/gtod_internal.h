@@ -324,6 +324,8 @@ void launch_scale_spectra(const SpecScaleArgs& a, hipStream_t s);
 void launch_panel(const PanelArgs& a, hipStream_t s);
 void launch_gemm_f32(const GemmArgs& a, hipStream_t s);
 void launch_gemm_bf16(const GemmArgs& a, hipStream_t s);
+// Rows and channels of a contraction's tiles, for a launch of so many panel rows.
+void contraction_tile(bool f16, int64_t rows, int K, int32_t tile[2]);
 // Bytes of the tiled halves of a Kp x Fp setup's responses, and the kernels
 // that build them (with the FP16 halves' channel scales e0, e1, unit0,
 // unit1) from the FP32 responses and the bins' scales d.

@@ -709,21 +709,24 @@ constexpr Shape kShapes[kNShapes] = {{256, 128, 256, 270.f, 210.f}, {256, 64, 25
                                      {128, 64, 256, 92.f, 85.f},    {64, 64, 256, 58.f, 58.f},
                                      {64, 32, 128, 46.f, 41.f}};
 
-template <bool F16>
-void launch_contract(const GemmArgs& a, hipStream_t s) {
-  const int64_t rows = (int64_t)a.n_pix * a.Tpad;
+int best_shape(bool f16, int64_t rows, int K) {
   int best = -1;
   float least = 0.f;
-  for (int q = a.K <= 64 ? 1 : 0; q < kNShapes; ++q) {
+  for (int q = K <= 64 ? 1 : 0; q < kNShapes; ++q) {
     const Shape& h = kShapes[q];
-    const int64_t wgs = (rows + h.rows - 1) / h.rows * ((a.K + h.channels - 1) / h.channels);
-    const float us = (float)((wgs + h.round - 1) / h.round) * (F16 ? h.f16_us : h.bf16_us);
+    const int64_t wgs = (rows + h.rows - 1) / h.rows * ((K + h.channels - 1) / h.channels);
+    const float us = (float)((wgs + h.round - 1) / h.round) * (f16 ? h.f16_us : h.bf16_us);
     if (best < 0 || us < least) {
       best = q;
       least = us;
     }
   }
-  switch (best) {
+  return best;
+}
+
+template <bool F16>
+void launch_contract(const GemmArgs& a, hipStream_t s) {
+  switch (best_shape(F16, (int64_t)a.n_pix * a.Tpad, a.K)) {
     case 0: launch_shape<F16, 4, 1, 4, 2, 4>(a, s); break;
     case 1: launch_shape<F16, 4, 1, 2, 2, 4>(a, s); break;
     case 2: launch_shape<F16, 2, 2, 1, 2, 4>(a, s); break;
@@ -733,6 +736,12 @@ void launch_contract(const GemmArgs& a, hipStream_t s) {
 }
 
 }  // namespace
+
+void contraction_tile(bool f16, int64_t rows, int K, int32_t tile[2]) {
+  const Shape& h = kShapes[best_shape(f16, rows, K)];
+  tile[0] = h.rows;
+  tile[1] = h.channels;
+}
 
 void launch_gemm_f32(const GemmArgs& a, hipStream_t s) { launch_contract<true>(a, s); }
 void launch_gemm_bf16(const GemmArgs& a, hipStream_t s) { launch_contract<false>(a, s); }

@@ -1678,6 +1678,14 @@ gtod_status gtod_convolve_screen(gtod_ctx* c, const double* in, int64_t nx, int6
   return GTOD_OK;
 }
 
+gtod_status gtod_contraction_tile(int32_t precision, int64_t rows, int32_t K, int32_t tile[2]) {
+  if ((precision != GTOD_PREC_FP32 && precision != GTOD_PREC_SPLIT_BF16) || rows < 1 || K < 1 ||
+      !tile)
+    return GTOD_EINVAL;
+  contraction_tile(precision == GTOD_PREC_FP32, rows, K, tile);
+  return GTOD_OK;
+}
+
 gtod_status gtod_free(gtod_ctx* c, int32_t kind, int32_t id) {
   if (!c) return GTOD_EINVAL;
   (void)hipSetDevice(c->device);

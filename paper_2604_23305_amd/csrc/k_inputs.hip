@@ -344,7 +344,7 @@ void launch_screen_conv(const ScreenConvArgs& a0, hipStream_t s) {
                             round(per_cu % resident);
     const bool shared = (int64_t)grid.x * grid.y > 256;
     const double per_row = n <= 8 ? (shared ? 1.08 : 0.78) : (shared ? 1.83 : 1.32);
-    const double by_strips = 5.0 + (a.strip + (n <= 8 ? 16 : 32)) * per_row;
+    const double by_strips = 5.0 + (std::min<int64_t>(a.strip, a.ny) + (n <= 8 ? 16 : 32)) * per_row;
     if (by_tiles < by_strips) {
       hipLaunchKernelGGL(k_screen_tile, dim3((unsigned)tiles), dim3(256), lds, s, a);
       return;

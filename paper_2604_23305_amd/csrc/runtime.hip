@@ -1289,14 +1289,15 @@ gtod_status gtod_reduce(gtod_ctx* c, const gtod_reduce_desc* d, void* hip_stream
   // channels each in turn, so that its time goes with T and the rounds of its
   // blocks (us sorted / unsorted: 7 spaxels x 30 channels x 3000 samples 71 /
   // 67, x 10000 88 / 125; 49 x 300 in 48 x 48 cells, 14 rounds, x 1000 243 /
-  // 300), and one or two channels share a sort badly (49 x 1 x 14000 133 / 124).
+  // 300), one or two channels share a sort badly (49 x 1 x 14000 133 / 124), and the
+  // atomics of a few cells collide (7 x 7 x 3950 in 2 x 2 cells 71 / 76).
   // Without maps the table of cosecants saves what two or more threads would
   // take of each (49 x 100 x 57600 1.12 / 1.24 ms, 49 x 1 93 / 70 us).
   bool fast = K > kRdChan || T <= 16384;
   if (maps) {
     const double blocks = (double)P * ((K + kRdGridChan - 1) / kRdGridChan);
     const double rounds = blocks / (256.0 * std::min<int64_t>(8, (160 << 10) / (C * 68)));
-    fast = (double)T * std::max(1.0, rounds) >= (K == 1 ? 16000 : K < 4 ? 8000 : 4800);
+    fast = (double)T * std::max(1.0, rounds) >= (K == 1 ? 16000 : K < 4 ? 8000 : C <= 25 ? 3300 : 4800);
   }
   // Room: with a thread's channels of the common-mode kernel beside it.  49
   // spaxels x 100 channels x 44000 samples in 64 MiB take 15.1 ms one channel at

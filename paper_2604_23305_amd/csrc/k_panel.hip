@@ -228,7 +228,7 @@ __device__ __forceinline__ f32x4 row_deviation(const Bins& b, int F, f32x4 t0, f
       *far += (uint32_t)__builtin_popcountll(__ballot(fabsf(dP[k]) > 0.125f * P));
     }
   };
-  if (!ANY_EL || (csc >= 0.f && csc < INFINITY))
+  if (!ANY_EL || __builtin_expect(csc >= 0.f && csc < INFINITY, 1))
     bins([](float x) { return one_minus_exp(x); }, [](uint32_t) { return false; });
   else
     bins([](float x) { return -expm1f(-x); }, [&](uint32_t j) { return j >= (uint32_t)F; });

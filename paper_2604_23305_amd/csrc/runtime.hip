@@ -738,12 +738,14 @@ gtod_status gtod_load_filters(gtod_ctx* c, const gtod_spectral_desc* d, int32_t*
     if (st == GTOD_OK) so.allocs.push_back(*p);
   };
   res((void**)&so.tau, (size_t)d->n_pwv * Fp * 4);
-  res((void**)&so.E, Fp * 4);
-  res((void**)&so.D, Fp * 4);
-  res((void**)&so.W, Fp * 4);
-  res((void**)&so.Pref, Fp * 4);
-  res((void**)&so.H, 4 * Fp * 4);
-  res((void**)&so.unscale, Fp * 4);
+  res((void**)&so.E, 9 * Fp * 4);
+  if (st == GTOD_OK) {
+    so.D = so.E + Fp;
+    so.W = so.D + Fp;
+    so.Pref = so.W + Fp;
+    so.H = so.Pref + Fp;
+    so.unscale = so.H + 4 * Fp;
+  }
   res((void**)&so.B, 3 * Kp * Fp * 4);
   res((void**)&so.Tb, tiled_response_bytes((int)Kp, (int)Fp, false));
   res((void**)&so.Th, tiled_response_bytes((int)Kp, (int)Fp, true));

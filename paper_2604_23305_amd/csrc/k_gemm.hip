@@ -689,11 +689,14 @@ void launch_shape(GemmArgs a, hipStream_t s) {
                      dim3((unsigned)(round_up(n_tt, 8) * a.n_cg)), dim3(64 * WR * WC * SPL), 0, s, a);
 }
 
-// One workgroup of a shape runs on a CU at a time (two of the 128 x 64
-// one), so a launch takes about the rounds of 256 workgroups times the time
-// of one, which these weights give: microseconds at 3000 bins, measured
-// with one round on an idle card (FP16 halves; BF16).  In launches of many
-// rounds 256 x 128 is the fastest per output: 43.2 ms of contractions in six
+// One workgroup of a shape runs on a CU at a time, so a launch takes about
+// the rounds of 256 workgroups times the time of one, which these weights
+// give: microseconds at 3000 bins, measured with one round on an idle card
+// (FP16 halves; BF16).  A CU holds two of the 128 x 64 one, but they take
+// nearly twice as long as one (256 of them 143 us, 512 253), so it counts by
+// rounds of 256 too.  In launches of many rounds the time goes with the tiles
+// rather than the rounds; the rule charges whole rounds there as well, which by
+// these weights may cost up to 10 % (96000 rows x 347 channels).  There 256 x 128 is the fastest per output: 43.2 ms of contractions in six
 // minutes of the 49-pixel, 347-channel IFU, against 47.4 with 256 x 64 and
 // 48.2 with 128 x 64; a launch of 160 rows takes 62 us with 64 x 64 tiles
 // against 261 with 256 x 128, and 50 with 64 x 32; but 198 workgroups of 64 x 32

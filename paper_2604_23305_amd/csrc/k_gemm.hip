@@ -696,9 +696,10 @@ void launch_shape(GemmArgs a, hipStream_t s) {
 // nearly twice as long as one (256 of them 143 us, 512 253), so it counts by
 // rounds of 256 too.  In launches of many rounds the time goes with the tiles
 // rather than the rounds; the rule charges whole rounds there as well, which by
-// these weights may cost up to 10 % (96000 rows x 347 channels).  There 256 x 128 is the fastest per output: 43.2 ms of contractions in six
-// minutes of the 49-pixel, 347-channel IFU, against 47.4 with 256 x 64 and
-// 48.2 with 128 x 64; a launch of 160 rows takes 62 us with 64 x 64 tiles
+// these weights may cost up to 10 % (96000 rows x 347 channels).  There 256 x
+// 128 is the fastest per output: 43.2 ms of contractions in six minutes of the
+// 49-pixel, 347-channel IFU, against 47.4 with 256 x 64 and 48.2 with 128 x 64;
+// a launch of 160 rows takes 62 us with 64 x 64 tiles
 // against 261 with 256 x 128, and 50 with 64 x 32; but 198 workgroups of 64 x 32
 // take 78 where 108 of 64 x 64 take 65 (operands from beyond the L2), so they
 // count by rounds of 128.  Up to 64 channels half of a 256 x 128 tile

@@ -25,13 +25,13 @@
 // depend on the order, only the cache traffic does.
 //
 // What bounds it: HBM.  A launch of 527k IFU rows writes 6.3 GB of panel and
-// fetches 1.35 GB (5.4 GB when a workgroup took 4 rows over all bins at a
-// time and read their corners again for the next 4) in 1.37 ms, 5.6 TB/s;
-// the five kernels together take 1.49 ms, against 2.43 ms before.  On the
+// fetches 0.89 GB (5.4 GB when a workgroup took 4 rows over all bins at a
+// time and read their corners again for the next 4) in 1.30 ms, 5.5 TB/s;
+// the five kernels together take 1.41 ms, against 2.37 ms before.  On the
 // way there it was bound by its instructions (41 per element with vector
 // records and the library's expm1f, 32 now) and by the panel's stores
 // displacing the tables from the L2: stored past the caches the sorted
-// kernel went from 1.70 to 1.37 ms.
+// kernel became a fifth faster.
 #include <hip/hip_runtime.h>
 
 #include "gtod_internal.h"
@@ -442,7 +442,7 @@ void launch_panel(const PanelArgs& a0, hipStream_t s) {
   // passes in one: 33621 rows 90 / 106, 42000 109 / 119, 56000 135 / 146, 84000
   // 200 / 206; against 8 rows, 3000 bins: 160 rows 11.7 / 20.4, 2800 rows 30.8 /
   // 36.2, at 7600 rows of 1500 bins no longer, 45.6 / 44.2); in longer launches a row's record serves all its passes (526848
-  // rows of 3000 bins: 1.59 ms, 1.64 with one pass each).
+  // rows of 3000 bins: 3 % less than with one pass each).
   a.rows_wg = rows < 1024 ? 2 : rows < 4096 ? 4 : rows < 1024 * kPanelRows ? 8
               : rows < 2048 * kPanelRows ? 16 : kPanelRows;
   static_assert(2 % kBatch == 0, "rows per workgroup");

@@ -16,7 +16,8 @@
 // without maps, T*), grid (T* and cell sums), combine (one thread per
 // (channel, cell)).  The common and grid kernels each stream the TOD once.
 //
-// The cosecants are tabulated once per call for all channels; each sample then
+// The cosecants are tabulated once per call for all channels (where that pays,
+// see gtod_reduce); each sample then
 // takes one FP64 expm1 (eta = 1 + expm1(ln eta), so 1 - eta keeps its relative
 // precision) and a division in either kernel, which is what bounds them.
 // (Polynomials in elevation in their place take 2.9 ms in all, but the last bits
@@ -26,12 +27,12 @@
 // summed by one thread per run of a cell and added to the block's sums in LDS,
 // without atomics except for cells of more than one run.
 //
-// 49 spaxels x 347 channels x 57600 samples, T* and 31 x 31 maps: 4.15 ms (8.37
+// 49 spaxels x 347 channels x 57600 samples, T* and 31 x 31 maps: 4.00 ms (8.37
 // with a sine and a division per spaxel, sample and four channels and two LDS
-// atomics per sample, which run at a lane per clock).  Common 1.03 ms (2.2
-// before), grid 2.97 (6.1): about 60 FP64 instructions a sample, 1.5 ms of the
+// atomics per sample, which run at a lane per clock).  Common 0.92 ms (2.2
+// before), grid 2.90 (6.1): about 60 FP64 instructions a sample, 1.5 ms of the
 // grid's time, beside 3.9 GB read and 4 GB written.  The sort, 70 us, serves all
-// channels.
+// channels.  Short series and few channels go without it (gtod_reduce).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
